@@ -37,6 +37,19 @@ def test_ragged_batch_matches_oracle():
     assert (got[1] == 0).all()
 
 
+@pytest.mark.parametrize("P,n", [(64, 9), (624, 17), (625, 5), (1249, 5), (2497, 3), (8193, 2)])
+def test_trajectory_lengths(P, n):
+    """Eight, four, two and one particle staged at a time (lengths at the edges of each), and a trajectory too long
+    to stage; more lags than one pass takes, unsorted and repeated; sums of n P products to 1e-12 of C(0)."""
+    rng = np.random.default_rng(P)
+    vel = rng.normal(0.0, 4.0, (P, n, 2))
+    lags = [int(l) for l in rng.permutation(np.concatenate([rng.integers(0, P, 66), [0, 0, 1, P - 1]]))]
+    offsets = [0, n // 2, n]
+    got = run(offsets, vel, lags)
+    ref = omd.vacf_sums(np.array(offsets), vel, lags)
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
 def test_md_velocities_and_lambda():
     import torch
 
