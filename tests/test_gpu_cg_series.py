@@ -122,6 +122,42 @@ def test_series_accumulates():
     assert np.allclose(m2, 2 * m1, rtol=1e-14)
 
 
+@pytest.mark.parametrize("case", ["edges", "far_drifts", "long", "longest", "large", "far_images"])
+def test_series_classification(case):
+    """Where the single-precision classification must give way to the definition or a pass is split: positions on cell
+    edges, drifts beyond four cells, trajectories of 214 and 427 snapshots (fewer particles staged at a time), more
+    particles than one group per block, images far from the box."""
+    import torch
+
+    import paper_2101_01160_amd as m
+    n, P, lx, lags, us = 130, 6, 8, [1, 3], [(0.0, 0.0), (0.25, -0.5), (0.1, 0.2), (-0.2, 0.1), (0.5, 0.5)]
+    if case == "far_drifts":
+        us = [(0.0, 0.0), (4.5, -0.25), (-3.0, 100.0)]
+    elif case == "long":
+        n, P, lags = 20, 214, [1, 32]
+    elif case == "longest":
+        n, P, lags = 10, 427, [1, 2, 3, 5, 7, 11]
+    elif case == "large":
+        n, P, lags, us = 2 * 262144 + 5, 3, [1], us[:2]
+    L = 16.0
+    xs, imgs = walk(n, L, P, 0.7, 77)
+    if case in ("edges", "far_drifts"):
+        xs = np.round(xs * 4.0) / 4.0  # cell edges, and the drifted ones, hit exactly
+        imgs = imgs + (xs >= L)
+        xs = np.where(xs >= L, xs - L, xs)
+    if case == "far_images":
+        imgs = imgs + np.int32(200_000_000)
+    imgs = np.ascontiguousarray(imgs, dtype=np.int32)
+    counts = torch.zeros((1, len(lags), len(us), 50), dtype=torch.int64, device="cuda")
+    moments = torch.zeros((1, len(lags), 5), dtype=torch.float64, device="cuda")
+    m.mdlg_coarse_grain_series([0, n], [L], [lx], torch.from_numpy(xs).cuda(), torch.from_numpy(imgs).cuda(), lags, us,
+                               counts, moments)
+    rc, rm = reference([(n, L, lx, 0.0)], xs, imgs, lags, us)
+    assert np.array_equal(counts.cpu().numpy(), rc)
+    mo = moments.cpu().numpy()
+    assert np.abs(mo - rm).max() <= 1e-12 * np.abs(rm).max()
+
+
 def test_series_invalid_arguments():
     import torch
 
