@@ -57,6 +57,18 @@ def test_random_walk_ensemble_matches_oracle(n, L, lx, P, step):
     assert np.array_equal(fo, rf) and np.array_equal(oo, ro)
 
 
+@pytest.mark.parametrize("n,lx,P,step", [(60001, 28, 18, 2.0), (60001, 29, 18, 1.5), (70000, 64, 17, 3.0),
+                                         (60001, 10, 18, 4.0), (20000, 25, 41, 2.0), (60001, 201, 18, 2.0),
+                                         (60001, 202, 18, 2.0), (4097, 7, 300, 2.0)])
+def test_counters_in_lds_match_oracle(n, lx, P, step):
+    """All 49 velocities, some of them, the rest velocity alone in LDS, and none; one to seven shares of a coarse step."""
+    L = 2.0 * lx
+    pos, img = walk(n, L, P, step, seed=lx)
+    f, o, x = gpu(L, lx, pos, img)
+    rf, ro, rx = omd.neq_mdlg(lx, L, [0, n], pos, img)
+    assert np.array_equal(f, rf) and np.array_equal(o, ro) and np.array_equal(x, rx)
+
+
 def test_cell_edges_and_box_side():
     L, lx, n, P = 25.0, 7, 512, 4
     rng = np.random.default_rng(4)
