@@ -272,8 +272,8 @@ mdlg_status mdlg_coarse_grain(const mdlg_lattice* lat, double box_l, int64_t n,
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  Same arguments, kernels and results (counts and moments bitwise
  * equal to mdlg_coarse_grain's); it calls no allocating routine.  Its moment
- * partials live in a fixed device array of the library (5.2 MB, one copy per
- * GPU, held until the process ends), which limits n to 2^25 = 33,554,432
+ * partials live in a fixed device array of the library (0.2 MB, one copy per
+ * GPU, held until the process ends).  n is limited to 2^25 = 33,554,432
  * particles: larger n is rejected with MDLG_EINVAL before anything is
  * launched.  The stream must belong to the current device.  Every call on a
  * GPU shares that GPU's array: calls that overlap on one GPU (on different

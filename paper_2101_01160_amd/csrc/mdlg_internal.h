@@ -68,11 +68,14 @@ __device__ __forceinline__ double wave_sum(double v) {
 // Lattice coordinate floor((x + shift) * inv), every operation rounded once,
 // exactly as written (no fused multiply-add), so that host and device agree
 // on the cell of a position bit for bit.
-__device__ __forceinline__ double lattice_qf(double x, double shift, double inv) {
+__device__ __forceinline__ double lattice_t(double x, double shift, double inv) {
 #pragma clang fp contract(off)
     double t = x + shift;
-    double u = t * inv;
-    return floor(u);
+    return t * inv;
+}
+
+__device__ __forceinline__ double lattice_qf(double x, double shift, double inv) {
+    return floor(lattice_t(x, shift, inv));
 }
 
 __device__ __forceinline__ long long lattice_q(double x, double shift, double inv) {

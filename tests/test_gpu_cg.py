@@ -65,6 +65,18 @@ def test_integer_displacements_and_overflow():
     assert c[49] > 0 and c.sum() == n
 
 
+@pytest.mark.parametrize("n,shift,k", [(3 * 1024 * 256 + 1, 0, 0), (5 * 1024 * 256 + 77, 0, 0), (5000, 1001, 0),
+                                       (5000, 100_000_000, 0), (5000, 0, 700_000_000), (5000, 0, -700_000_000)])
+def test_block_limit_and_wide_coordinates(n, shift, k):
+    """More particles than one pass of the most blocks takes; image differences and lattice coordinates on either side
+    of what the 32-bit path holds (particles that stay, and some whose images differ by `shift`)."""
+    rng = np.random.default_rng(n)
+    lx, L = 20, 40.0
+    x0, x1, i0, i1 = src.gaussian_step(rng, n, L, var=(0.8 * L / lx) ** 2)
+    i1 = i1 + shift * (np.arange(n)[:, None] % 7 == 0)
+    compare(lx, L, x0, x1, i0, i1, k0=k, k1=k + 1, u=(0.25, -0.125) if k else (0.0, 0.0))
+
+
 def test_images_and_frame_shift():
     rng = np.random.default_rng(2)
     lx, L, n = 50, 100.0, 50_000
