@@ -103,8 +103,10 @@ typedef struct {
                                the two-step tiles are (dilute systems, where
                                the halo is cheap), else one; 1 = one; 2 = two
                                wherever the geometry allows; 3 = three wherever
-                               it allows, else two.  Results are the same bit
-                               for bit.                                        */
+                               it allows, else two.  0 also lets one block take
+                               a whole replica through a call where every replica
+                               has at most 2048 particles.  Results are the same
+                               bit for bit.                                    */
 } lj_params;
 
 typedef struct lj_md lj_md; /* opaque handle; owns all device state */
@@ -205,7 +207,8 @@ typedef struct {
     int32_t cells_per_side; /* cell-list cells per side of replica 0            */
     int32_t block_size;
     double cell_width;      /* of replica 0                                     */
-    int32_t steps_per_launch; /* ordinary MD steps per step-kernel launch: 1, 2 or 3 */
+    int32_t steps_per_launch; /* ordinary MD steps per step-kernel launch on the replicas' geometry: 1, 2 or 3
+                                 (replicas of up to 2048 particles take whole calls in one launch by default) */
     int32_t reserved;
 } lj_md_info_t;
 mdlg_status lj_md_info(const lj_md* md, lj_md_info_t* info);

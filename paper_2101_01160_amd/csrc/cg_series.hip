@@ -39,6 +39,7 @@ constexpr int kSeriesMaxLag = 32;   // ring depth
 constexpr int kSeriesMaxLags = 32;
 constexpr int kSeriesMaxU = 16;
 constexpr int kSeriesMaxJobs = 256;
+constexpr int kSeriesLds = 150 * 1024;  // dynamic LDS of one block at most
 
 struct SeriesBlock {
     long long start;  // first particle (index into n_tot)
@@ -399,7 +400,7 @@ extern "C" mdlg_status mdlg_coarse_grain_series(int32_t n_rep, const int64_t* of
     const int nup = (n_u + kSeriesU - 1) / kSeriesU * kSeriesU;
     const size_t lds_counts = (size_t)ring * kSeriesBS * sizeof(int2) + (size_t)n_lag * nup * MDLG_NCOUNTS * 4;
     const size_t lds_disp = (size_t)n_snap * pt * (sizeof(double2) + sizeof(int2));
-    if (lds_counts > 150 * 1024 || lds_disp > 150 * 1024)
+    if (lds_counts > kSeriesLds || lds_disp > kSeriesLds)
         return fail(MDLG_EINVAL, std::string(who) + "lags and drifts exceed the LDS budget");
     double u_max = 0.0;
     for (int t = 0; t < 2 * n_u; ++t) u_max = std::max(u_max, std::fabs(u[t]));
@@ -463,7 +464,7 @@ extern "C" mdlg_status mdlg_coarse_grain_series(int32_t n_rep, const int64_t* of
     if (e == hipSuccess) {
         auto launch = [&](auto kernel) {
             hipError_t le = hipSuccess;
-            if (lds_counts > 64 * 1024) le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_counts);
+            if (lds_counts > 64 * 1024) le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kSeriesLds);
             if (le != hipSuccess) return le;
             hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kSeriesBS), lds_counts, st, a);
             return hipGetLastError();
@@ -474,7 +475,7 @@ extern "C" mdlg_status mdlg_coarse_grain_series(int32_t n_rep, const int64_t* of
     if (e == hipSuccess && moments) {
         auto launch = [&](auto kernel) {
             hipError_t le = hipSuccess;
-            if (lds_disp > 32 * 1024) le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_disp);
+            if (lds_disp > 32 * 1024) le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kSeriesLds);
             if (le != hipSuccess) return le;
             hipLaunchKernelGGL(kernel, dim3((unsigned)ndb), dim3(kDispBS), lds_disp, st, a);
             return hipGetLastError();

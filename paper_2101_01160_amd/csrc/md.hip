@@ -844,9 +844,82 @@ __device__ __forceinline__ void list_rows(const Entry* __restrict__ list, unsign
     for (int u = 0; u < N; ++u) kk[u] = list[off + u * stride];
 }
 
+// Adds the force of a pair at separation (dx, dy) where `valid` and inside the
+// cutoff, to ax and ay or (F32) bx and by.  The fused multiply-adds whose choice
+// is the compiler's otherwise are written out, so that every kernel rounds alike.
+template <bool F32>
+__device__ __forceinline__ void pair_add(double dx, double dy, bool valid, double rc2, double eps24, float rc2f,
+                                         float eps24f, double& ax, double& ay, float& bx, float& by) {
+    if (F32) {
+        const float fdx = (float)dx, fdy = (float)dy;
+        const float r2 = fmaf(fdx, fdx, fdy * fdy);
+        const float ir2 = __builtin_amdgcn_rcpf(r2);
+        const float ir2n = ir2 * fmaf(-r2, ir2, 2.0f);
+        const float ir6 = ir2n * ir2n * ir2n;
+        float fr = eps24f * ir6 * (2.0f * ir6 - 1.0f) * ir2n;
+        fr = (valid && r2 < rc2f) ? fr : 0.0f;
+        bx = fmaf(fr, fdx, bx);
+        by = fmaf(fr, fdy, by);
+    } else {
+        const double r2 = fma(dx, dx, dy * dy);
+        const double ir2 = recip(r2);
+        const double ir6 = ir2 * ir2 * ir2;
+        double fr = eps24 * ir6 * (2.0 * ir6 - 1.0) * ir2;
+        fr = (valid && r2 < rc2) ? fr : 0.0;
+        ax = fma(fr, dx, ax);
+        ay = fma(fr, dy, ay);
+    }
+}
+
+// The same for U pairs, stage by stage: U independent chains in flight where
+// few waves share a SIMD.  The sums are taken in order, with the same roundings.
+template <bool F32, int U>
+__device__ __forceinline__ void pairs_add(const double (&dx)[U], const double (&dy)[U], const bool (&valid)[U], double rc2,
+                                          double eps24, float rc2f, float eps24f, double& ax, double& ay, float& bx,
+                                          float& by) {
+    if (F32) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) pair_add<F32>(dx[u], dy[u], valid[u], rc2, eps24, rc2f, eps24f, ax, ay, bx, by);
+        return;
+    }
+    double r2[U], ir2[U], e[U], ir6[U], fr[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r2[u] = dy[u] * dy[u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) r2[u] = fma(dx[u], dx[u], r2[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) ir2[u] = __builtin_amdgcn_rcp(r2[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = fma(-r2[u], ir2[u], 1.0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = fma(e[u], e[u], e[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) ir2[u] = fma(e[u], ir2[u], ir2[u]);
+#pragma unroll
+    for (int u = 0; u < U; ++u) ir6[u] = ir2[u] * ir2[u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) ir6[u] = ir6[u] * ir2[u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        fr[u] = eps24 * ir6[u];
+        e[u] = fma(2.0, ir6[u], -1.0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) fr[u] = fr[u] * e[u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) fr[u] = fr[u] * ir2[u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) fr[u] = (valid[u] && r2[u] < rc2) ? fr[u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        ax = fma(fr[u], dx[u], ax);
+        ay = fma(fr[u], dy[u], ay);
+    }
+}
+
 // With use_first, the rows of the passes that lie within the first P come
 // from `first`.
-template <bool F32, int U, int P, typename Entry, typename Fetch>
+template <bool F32, int U, int P, bool STAGED = false, typename Entry, typename Fetch>
 __device__ __forceinline__ void nlist_force(double2 p, int nn, const Entry* __restrict__ list, unsigned int off,
                                             unsigned int stride, Fetch fetch, bool interior, double L, double invL,
                                             double rc2, double eps24, float rc2f, float eps24f, double& fx,
@@ -870,6 +943,25 @@ __device__ __forceinline__ void nlist_force(double2 p, int nn, const Entry* __re
         double2 q[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) q[u] = fetch(kk[u]);
+        if constexpr (STAGED) {
+            double dx[U], dy[U];
+            bool valid[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                valid[u] = j0 + u < nn;
+                dx[u] = p.x - q[u].x;
+                dy[u] = p.y - q[u].y;
+            }
+            if (!interior) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    dx[u] = min_image_rint(dx[u], L, invL);
+                    dy[u] = min_image_rint(dy[u], L, invL);
+                }
+            }
+            pairs_add<F32, U>(dx, dy, valid, rc2, eps24, rc2f, eps24f, ax, ay, bx, by);
+            continue;
+        }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const bool valid = j0 + u < nn;
@@ -881,25 +973,7 @@ __device__ __forceinline__ void nlist_force(double2 p, int nn, const Entry* __re
             // entries past the list (index 0: any staged particle, or the particle
             // itself) are computed and then dropped with the cutoff test; a zero
             // separation gives a NaN there, which the select discards
-            if (F32) {
-                const float fdx = (float)dx, fdy = (float)dy;
-                const float r2 = fdx * fdx + fdy * fdy;
-                const float ir2 = __builtin_amdgcn_rcpf(r2);
-                const float ir2n = ir2 * (2.0f - r2 * ir2);
-                const float ir6 = ir2n * ir2n * ir2n;
-                float fr = eps24f * ir6 * (2.0f * ir6 - 1.0f) * ir2n;
-                fr = (valid && r2 < rc2f) ? fr : 0.0f;
-                bx += fr * fdx;
-                by += fr * fdy;
-            } else {
-                const double r2 = dx * dx + dy * dy;
-                const double ir2 = recip(r2);
-                const double ir6 = ir2 * ir2 * ir2;
-                double fr = eps24 * ir6 * (2.0 * ir6 - 1.0) * ir2;
-                fr = (valid && r2 < rc2) ? fr : 0.0;
-                ax += fr * dx;
-                ay += fr * dy;
-            }
+            pair_add<F32>(dx, dy, valid, rc2, eps24, rc2f, eps24f, ax, ay, bx, by);
         }
     }
     fx = F32 ? (double)bx : ax;
@@ -918,19 +992,20 @@ __device__ __forceinline__ void nlist_force(double2 p, int nn, const Entry* __re
 
 // Velocity-Verlet update with the force at the current position: complete
 // the half-step velocity (not on the first step, whose velocity is a full-step
-// one), kick, drift, wrap into [0, L) with the image change in (wx, wy).
+// one), kick, drift, wrap into [0, L) with the image change in (wx, wy).  The
+// fused multiply-adds are written out so that every kernel rounds alike.
 template <bool FIRST, bool WRAP = true>
 __device__ __forceinline__ double2 vv_update(double2 p, double2& v, double fx, double fy, double dt, double hdt,
                                              double L, int& wx, int& wy) {
     if (!FIRST) {
-        v.x = v.x + hdt * fx;
-        v.y = v.y + hdt * fy;
+        v.x = fma(hdt, fx, v.x);
+        v.y = fma(hdt, fy, v.y);
     }
-    v.x = v.x + hdt * fx;
-    v.y = v.y + hdt * fy;
+    v.x = fma(hdt, fx, v.x);
+    v.y = fma(hdt, fy, v.y);
     double2 pn;
-    pn.x = p.x + dt * v.x;
-    pn.y = p.y + dt * v.y;
+    pn.x = fma(dt, v.x, p.x);
+    pn.y = fma(dt, v.y, p.y);
     wx = 0;
     wy = 0;
     if (!WRAP) return pn;  // the caller knows that no particle reaches the box edge
@@ -1613,6 +1688,451 @@ __global__ __launch_bounds__(BS) void k_pair_build(const int* __restrict__ cs, c
     }
 }
 
+// Small replicas: one block holds a whole replica for a whole call.
+//
+// A replica of up to kResMax particles fits in one compute unit: positions in
+// LDS (ping-pong), everything else of a particle in the registers of one
+// thread, neighbour lists in LDS.  The block then takes all steps of a call
+// (up to kResSteps) with one barrier per step, rebuilding its cells and lists
+// every K steps by itself: no launches, no halo and no HBM traffic in between.
+// With three steps per launch on tiles a launch of such a system took 6.1 us
+// (512 particles) to 11.5 us (256 replicas of 998), the seven launches of a
+// rebuild 33 us; the time per step including rebuilds was 2.9 us (512
+// particles) and 5.7 us (256 x 998), here 1.1 and 1.75 us.  A step without any
+// pair takes 0.35 us (barrier, position write and read, update); the rest is
+// the issue of FP64 instructions, about 25 per list entry.
+//
+// Slots, cells and lists are those of the other step kernels (particles within
+// a cell ordered by caller index, list entries in cell order), and so is the
+// arithmetic: the same positions and velocities bit for bit.  After each
+// rebuild threads take the particles ordered by list length, since a wave runs
+// as many passes as its longest list.
+constexpr int kResBS = 1024;
+constexpr int kResMax = 2 * kResBS;       // particles of one replica at most
+constexpr int kResLds = 156 * 1024;       // dynamic LDS at most
+constexpr int kResSteps = 4096;           // steps of one launch at most (a few milliseconds)
+constexpr int kResGroups = 16;            // list-length groups of the thread order
+
+struct ResArgs {
+    StepArgs s;
+    int2* img;
+    int* id;
+    int* cs;
+    short* nbl;
+    unsigned char* nbc;
+    double2* pref;
+    unsigned long long* counts;
+    double* moments;
+    int cap, cells, rows;       // LDS extents: slots, cells, list rows
+    int maxnb;                  // list rows in all: those past `rows` stay in nbl
+    int nsteps, K, since;       // steps of this launch; rebuild interval; steps since the last rebuild
+    int first;                  // the first step's velocity is a full-step one
+    int s_cg;                   // 0: no coarse-graining
+    int to_event;               // steps until the next event (1 .. s_cg)
+    long long event;            // index of that coarse step
+};
+
+// Exclusive scan over a block of whole waves; lds holds 32 ints.
+__device__ __forceinline__ int res_scan(int v, int* lds, int& total) {
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    int x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    __syncthreads();  // earlier use of lds
+    if (lane == 63) lds[wid] = x;
+    __syncthreads();
+    int off = 0;
+    total = 0;
+    for (int w = 0; w < nw; ++w) {
+        const int t = lds[w];
+        off += w < wid ? t : 0;
+        total += t;
+    }
+    return off + x - v;
+}
+
+template <bool F32, int NP, int U>
+__global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ int scan[32];
+    __shared__ int ghist[kResGroups][NP * kResBS / 64];
+    __shared__ int hist[MDLG_NCOUNTS];
+    __shared__ double red[kResBS / 64][4];
+    __shared__ double macc[MDLG_NMOMENTS];
+    const int r = blockIdx.x, tid = threadIdx.x, BS = blockDim.x, lane = tid & 63, wave = tid >> 6;
+    const RepDev& R = a.s.reps[r];
+    // held in registers: a read through R after a barrier is a new load
+    const int n = R.n, nc = R.nc, slot0 = R.slot0, cells = nc * nc, S = a.s.nslots;
+    const double L = R.L, halfL = R.halfL, invL = 1.0 / L, inv_w = R.inv_w, rl2 = R.w * R.w, rc2 = R.rc2, eps24 = R.eps24;
+    const double skin2 = R.skin_half * R.skin_half, dt = a.s.dt, hdt = a.s.hdt;
+    const float rc2f = R.rc2f, eps24f = R.eps24f;
+    double2* xa = reinterpret_cast<double2*>(smem);                                    // [cap]
+    double2* xb = xa + a.cap;                                                          // [cap]
+    unsigned short* start = reinterpret_cast<unsigned short*>(xb + a.cap);             // [cells + 1]
+    unsigned short* lst = start + (a.cells + 8) / 8 * 8;                               // [rows][cap]
+    // rebuild scratch, in the lists' place until they are written
+    int* cnt = reinterpret_cast<int*>(lst);                                            // [cells]
+    int* permid = cnt + a.cells;                                                       // [cap]
+    unsigned short* order = reinterpret_cast<unsigned short*>(xb);                     // [cap] slot of each place
+    // a thread's particles: their slot, state, list length and first list rows
+    int slot[NP], id[NP], nn[NP], pre[NP][kListPre];
+    double2 p[NP], v[NP], snap[NP], pref[NP];
+    int2 img[NP];
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        const int q = tid + k * BS;
+        const int s = slot0 + (q < n ? q : 0);
+        slot[k] = q;
+        p[k] = a.s.pin[s];
+        v[k] = a.s.vel[s];
+        img[k] = a.img[s];
+        id[k] = a.id[s];
+        snap[k] = a.s_cg ? a.s.snap[s] : make_double2(0.0, 0.0);
+        pref[k] = a.pref[s];
+        nn[k] = 0;
+        if (q < n) xa[q] = p[k];
+    }
+    // list entries in nbl: the slot relative to the particle's, modulo n in [-n/2, n/2)
+    auto put = [&](int j, int q, int e) __attribute__((always_inline)) {
+        e -= q;
+        if (2 * e >= n) e -= n;
+        else if (2 * e < -n) e += n;
+        a.nbl[(long long)j * S + slot0 + q] = (short)e;
+    };
+    auto get = [&](int j, int q) __attribute__((always_inline)) {
+        const int e = q + a.nbl[(long long)j * S + slot0 + q];
+        return e < 0 ? e + n : (e >= n ? e - n : e);
+    };
+    if (tid < MDLG_NCOUNTS) hist[tid] = 0;
+    if (a.s_cg && tid < MDLG_NMOMENTS) macc[tid] = a.moments[r * MDLG_NMOMENTS + tid];
+    int since = a.since;
+    bool rebuilt = false;
+
+    // Particles two cells or more from every box edge have no neighbour across
+    // it until the next rebuild, and neither they nor their neighbours reach it:
+    // a wave of them needs no image and no wrap (`inner`).
+    auto near_edge = [&](double2 w) __attribute__((always_inline)) {
+        const int cx = cell_coord(w.x, inv_w, nc), cy = cell_coord(w.y, inv_w, nc);
+        return !(cx >= 2 && cx < nc - 2 && cy >= 2 && cy < nc - 2);
+    };
+    // threads take the particles in order of list length, longest first, those
+    // near an edge before the others: a stable counting sort of the slots
+    auto deal = [&]() __attribute__((always_inline)) {
+        constexpr int half = kResGroups / 2;
+        int g[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            g[k] = slot[k] < n ? min((nn[k] + U - 1) / U, half - 1) + (near_edge(pref[k]) ? half : 0) : -1;
+        int rank[NP];
+        for (int e = 0; e < kResGroups; ++e) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                const unsigned long long m = __ballot(g[k] == e);
+                if (g[k] == e) rank[k] = __popcll(m & ((1ull << lane) - 1ull));
+                if (lane == 0) ghist[e][k * (BS >> 6) + wave] = __popcll(m);
+            }
+        }
+        __syncthreads();
+        const int nw = NP * (BS >> 6), tot = kResGroups * nw;  // <= BS, see the launch
+        int unused, val = 0;
+        const int e = tid < tot ? kResGroups - 1 - tid / nw : 0, w = tid < tot ? tid % nw : 0;
+        if (tid < tot) val = ghist[e][w];
+        const int base = res_scan(val, scan, unused);
+        if (tid < tot) ghist[e][w] = base;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            if (g[k] >= 0) order[ghist[g[k]][k * (BS >> 6) + wave] + rank[k]] = (unsigned short)slot[k];
+        __syncthreads();
+    };
+    // after deal(): each thread's new slots, and the first rows of their lists
+    bool inner[NP];
+    auto lists = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            inner[k] = __ballot(slot[k] < n && near_edge(pref[k])) == 0ull;
+#pragma unroll
+            for (int u = 0; u < kListPre; ++u) pre[k][u] = u < a.rows && slot[k] < n ? lst[u * a.cap + slot[k]] : 0;
+        }
+    };
+
+    auto rebuild = [&]() __attribute__((always_inline)) {
+        __syncthreads();
+        for (int c = tid; c < cells; c += BS) cnt[c] = 0;
+        __syncthreads();
+        int cell[NP], rank[NP], dst[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (slot[k] >= n) continue;
+            cell[k] = cell_coord(p[k].y, inv_w, nc) * nc + cell_coord(p[k].x, inv_w, nc);
+            rank[k] = atomicAdd(&cnt[cell[k]], 1);
+            const double ex = fabs(min_image(p[k].x - pref[k].x, L, halfL));
+            const double ey = fabs(min_image(p[k].y - pref[k].y, L, halfL));
+            if (!(ex * ex + ey * ey <= skin2)) atomicOr(a.s.err, ERR_SKIN);
+            if (!isfinite(p[k].x) || !isfinite(p[k].y) || !isfinite(v[k].x) || !isfinite(v[k].y))
+                atomicOr(a.s.err, ERR_NONFINITE);
+        }
+        __syncthreads();
+        const int per = (cells + BS - 1) / BS, c0 = tid * per, c1 = min(c0 + per, cells);
+        int sum = 0;
+        for (int c = c0; c < c1; ++c) sum += cnt[c];
+        int total;
+        int at = res_scan(sum, scan, total);
+        for (int c = c0; c < c1; ++c) {
+            start[c] = (unsigned short)at;
+            at += cnt[c];
+        }
+        if (tid == 0) start[cells] = (unsigned short)n;
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            if (slot[k] < n) permid[start[cell[k]] + rank[k]] = id[k];
+        __syncthreads();
+        // the slot within the cell follows from the caller index
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (slot[k] >= n) continue;
+            const int lo = start[cell[k]], hi = start[cell[k] + 1];
+            dst[k] = lo;
+            for (int e = lo; e < hi; ++e) dst[k] += permid[e] < id[k] ? 1 : 0;
+            xa[dst[k]] = p[k];
+        }
+        __syncthreads();
+        // lists of slot q by thread q: the slots within rc + skin in cell order
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int q = tid + k * BS;
+            if (q >= n) continue;
+            const double2 w = xa[q];
+            const int cx = cell_coord(w.x, inv_w, nc), cy = cell_coord(w.y, inv_w, nc);
+            int c = 0;
+            for (int oy = -1; oy <= 1; ++oy) {
+                int rw = cy + oy;
+                rw = rw < 0 ? rw + nc : (rw >= nc ? rw - nc : rw);
+                const int base = rw * nc;
+                const int xl = cx > 0 ? cx - 1 : 0, xr = cx < nc - 1 ? cx + 2 : nc;
+                const bool edge = cx == 0 || cx == nc - 1;
+                const int xw = cx == 0 ? nc - 1 : 0;
+                const int a0 = start[base + xl], a1 = start[base + xr];
+                const int b0 = edge ? start[base + xw] : 0, b1 = edge ? start[base + xw + 1] : 0;
+                const int na = a1 - a0, tot = na + (b1 - b0);
+                for (int t = 0; t < tot; ++t) {
+                    const int e = t < na ? a0 + t : b0 + (t - na);
+                    if (e == q) continue;
+                    const double2 z = xa[e];
+                    const double dx = min_image_rint(w.x - z.x, L, invL), dy = min_image_rint(w.y - z.y, L, invL);
+                    if (within_list_range(dx, dy, rl2)) {
+                        if (c < a.rows) lst[c * a.cap + q] = (unsigned short)e;
+                        else if (c < a.maxnb) put(c, q, e);
+                        ++c;
+                    }
+                }
+            }
+            if (c > a.maxnb) {
+                atomicOr(a.s.err, ERR_NLIST);
+                c = a.maxnb;
+            }
+            nn[k] = c;
+            slot[k] = q;
+            pref[k] = w;
+        }
+        __syncthreads();  // rows past a.rows are read by other threads of the block, from its own L1
+        deal();
+        // hand the particles over: their old thread writes to the slot's place
+        int mine[NP], len[NP];
+#pragma unroll
+        for (int k = 0; k < NP; ++k) mine[k] = tid + k * BS < n ? order[tid + k * BS] : n;
+        unsigned short* lens = order + a.cap;  // [cap] list length of each slot
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            if (tid + k * BS < n) lens[tid + k * BS] = (unsigned short)nn[k];
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NP; ++k) len[k] = mine[k] < n ? lens[mine[k]] : 0;
+        __syncthreads();
+        auto hand = [&](double2 (&w)[NP]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int k = 0; k < NP; ++k)
+                if (tid + k * BS < n) xb[dst[k]] = w[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < NP; ++k)
+                if (mine[k] < n) w[k] = xb[mine[k]];
+            __syncthreads();
+        };
+        hand(v);
+        if (a.s_cg) hand(snap);
+        int4* xi = reinterpret_cast<int4*>(xb);
+#pragma unroll
+        for (int k = 0; k < NP; ++k)
+            if (tid + k * BS < n) xi[dst[k]] = make_int4(img[k].x, img[k].y, id[k], 0);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            slot[k] = mine[k];
+            nn[k] = len[k];
+            if (mine[k] < n) {
+                const int4 t = xi[mine[k]];
+                img[k] = make_int2(t.x, t.y);
+                id[k] = t.z;
+                p[k] = xa[mine[k]];
+                pref[k] = p[k];
+            }
+        }
+        lists();
+        __syncthreads();
+        since = 0;
+        rebuilt = true;
+    };
+
+    // lists left by the launch before
+    if (since < a.K) {
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int q = tid + k * BS;
+            if (q >= n) continue;
+            nn[k] = a.nbc[slot0 + q];  // (pref is that of slot q)
+            for (int j = 0; j < min(nn[k], a.rows); ++j) lst[j * a.cap + q] = (unsigned short)get(j, q);
+        }
+        __syncthreads();
+        deal();
+        // every particle's state is still in global memory: read it again in the new order
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int q = tid + k * BS < n ? order[tid + k * BS] : n;
+            slot[k] = q;
+            const int s = slot0 + (q < n ? q : 0);
+            p[k] = a.s.pin[s];
+            v[k] = a.s.vel[s];
+            img[k] = a.img[s];
+            id[k] = a.id[s];
+            if (a.s_cg) snap[k] = a.s.snap[s];
+            pref[k] = a.pref[s];
+            nn[k] = q < n ? a.nbc[s] : 0;
+        }
+        lists();
+    }
+    __syncthreads();
+
+    int to_event = a.to_event;
+    long long event = a.event;
+    for (int st = 0; st < max(a.nsteps, 1); ++st) {
+        if (since >= a.K) rebuild();
+        if (a.nsteps == 0) break;
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            if (slot[k] >= n) continue;
+            const int q = slot[k];
+            auto fetch = [&](int e) { return xa[e]; };
+            double fx, fy;
+            nlist_force<F32, U, kListPre, true>(p[k], min(nn[k], a.rows), (const unsigned short*)lst, (unsigned)q, (unsigned)a.cap,
+                                          fetch, inner[k], L, invL, rc2, eps24, rc2f, eps24f, fx, fy, pre[k], true);
+            if (nn[k] > a.rows) {  // rare: lists beyond LDS
+                float bx = (float)fx, by = (float)fy;
+                for (int j = a.rows; j < nn[k]; ++j) {
+                    const double2 z = xa[get(j, q)];
+                    pair_add<F32>(min_image_rint(p[k].x - z.x, L, invL), min_image_rint(p[k].y - z.y, L, invL), true, rc2, eps24,
+                                  rc2f, eps24f, fx, fy, bx, by);
+                }
+                if (F32) {
+                    fx = (double)bx;
+                    fy = (double)by;
+                }
+            }
+            int wx, wy;
+            if (!a.first || st > 0) {
+                v[k].x = fma(hdt, fx, v[k].x);
+                v[k].y = fma(hdt, fy, v[k].y);
+            }
+            if (inner[k]) {
+                p[k] = vv_update<true, false>(p[k], v[k], fx, fy, dt, hdt, L, wx, wy);
+            } else {
+                p[k] = vv_update<true>(p[k], v[k], fx, fy, dt, hdt, L, wx, wy);
+                img[k].x += wx;
+                img[k].y += wy;
+            }
+            xb[q] = p[k];
+        }
+        ++since;
+        if (a.s_cg && --to_event == 0) {
+            double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;
+            int rest = 0;
+#pragma unroll
+            for (int k = 0; k < NP; ++k) {
+                if (slot[k] >= n) continue;
+                long long cell;
+                const int idx = cg_index(R, event, p[k], snap[k], cell);
+                if (idx < MDLG_NQ && a.s.cell_acc)
+                    atomicAdd(&a.s.cell_acc[R.cacc0 + (long long)idx * R.lx * R.lx + cell], 1);
+                if (idx == 0) ++rest;
+                else atomicAdd(&hist[idx], 1);
+                const double dx = min_image(p[k].x - snap[k].x, L, halfL);
+                const double dy = min_image(p[k].y - snap[k].y, L, halfL);
+                const double dx2 = dx * dx, dy2 = dy * dy;
+                m0 += dx2 + dy2;
+                m1 += dx2 * dx2 + dy2 * dy2;
+                m2 += dx;
+                m3 += dy;
+                snap[k] = p[k];
+            }
+            for (int o = 32; o > 0; o >>= 1) rest += __shfl_xor(rest, o, 64);
+            m0 = wave_sum(m0);
+            m1 = wave_sum(m1);
+            m2 = wave_sum(m2);
+            m3 = wave_sum(m3);
+            if (lane == 0) {
+                if (rest) atomicAdd(&hist[0], rest);
+                red[wave][0] = m0;
+                red[wave][1] = m1;
+                red[wave][2] = m2;
+                red[wave][3] = m3;
+            }
+            __syncthreads();
+            if (tid < 4) {
+                double sum = 0.0;
+                for (int w = 0; w < (BS >> 6); ++w) sum += red[w][tid];
+                macc[1 + tid] += sum;
+            }
+            if (tid == 4) macc[0] += 2.0 * (double)n;
+            to_event = a.s_cg;
+            ++event;
+        }
+        __syncthreads();
+        double2* t = xa;
+        xa = xb;
+        xb = t;
+        order = reinterpret_cast<unsigned short*>(xb);
+    }
+
+    // back to global memory, as the other step kernels leave it
+#pragma unroll
+    for (int k = 0; k < NP; ++k) {
+        if (slot[k] >= n) continue;
+        const int s = slot0 + slot[k];
+        if (!isfinite(p[k].x) || !isfinite(p[k].y) || !isfinite(v[k].x) || !isfinite(v[k].y)) atomicOr(a.s.err, ERR_NONFINITE);
+        a.s.pout[s] = p[k];
+        a.s.vel[s] = v[k];
+        a.img[s] = img[k];
+        if (a.s_cg) a.s.snap[s] = snap[k];
+        if (rebuilt) {
+            a.id[s] = id[k];
+            a.pref[s] = pref[k];
+            a.nbc[s] = (unsigned char)nn[k];
+            if (since < a.K) {
+                for (int j = 0; j < min(nn[k], a.rows); ++j) put(j, slot[k], lst[j * a.cap + slot[k]]);
+            }
+        }
+    }
+    if (rebuilt)
+        for (int c = tid; c <= cells; c += BS) a.cs[R.cell0 + c] = slot0 + start[c];
+    if (a.s_cg) {
+        if (tid < MDLG_NCOUNTS && hist[tid]) a.counts[r * MDLG_NCOUNTS + tid] += (unsigned long long)hist[tid];
+        if (tid < MDLG_NMOMENTS) a.moments[r * MDLG_NMOMENTS + tid] = macc[tid];
+    }
+}
+
 // The finish as a kernel of its own (one block per replica and component).
 __global__ __launch_bounds__(kFinishBS) void k_cg_finish(const int* __restrict__ hpart, const double* __restrict__ mpart,
                                                          int pstride, const RepDev* __restrict__ reps,
@@ -2051,6 +2571,12 @@ struct lj_md {
     unsigned char* tcnt = nullptr;    // [npt][kPairCap]
     double2* pref = nullptr;  // positions at the list build
     int maxnb = 0;
+    // a block per replica for whole calls (see k_resident); steps_per_launch is
+    // then what the replicas' geometry would allow the tiles
+    bool resident = false;
+    int spl = 1;
+    int res_bs = 0, res_np = 0, res_cap = 0, res_cells = 0, res_rows = 0;
+    size_t res_lds = 0;
     int* d_hpart = nullptr;
     int pstride = 0;  // tiles per component row of the partials (the most of any kind of tile)
     double2* pos[2] = {nullptr, nullptr};
@@ -2474,6 +3000,59 @@ int steps_to_alignment(const lj_md* md) {
     return r == 0 ? 0 : (int)(period - r);
 }
 
+// `count` steps of a resident handle (count 0: a due rebuild alone).
+hipError_t run_resident(lj_md* md, hipStream_t st, long long count) {
+    hipError_t e = hipSuccess;
+    do {
+        ResArgs a{};
+        a.s = make_args(md);
+        a.s.pout = md->pos[md->ppar];  // in place: a block alone reads and writes its replica
+        a.img = md->img[md->opar];
+        a.id = md->id[md->opar];
+        a.cs = md->cs;
+        a.nbl = md->nbl;
+        a.nbc = md->nbc;
+        a.pref = md->pref;
+        a.counts = md->counts;
+        a.moments = md->moments;
+        a.cap = md->res_cap;
+        a.cells = md->res_cells;
+        a.rows = md->res_rows;
+        a.maxnb = md->maxnb;
+        a.nsteps = (int)std::min<long long>(count, kResSteps);
+        a.K = md->K;
+        a.since = md->since_rebuild;
+        a.first = md->vel_full ? 1 : 0;
+        a.s_cg = md->cg_on ? md->s_cg : 0;
+        a.to_event = md->cg_on ? (int)(md->s_cg - md->cg_t % md->s_cg) : 0;
+        a.event = md->events + 1;
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(md->R), dim3(md->res_bs), md->res_lds, st, a);
+            return hipGetLastError();
+        };
+        // up to 512 particles two waves share a SIMD and the chain of a pass counts: four entries per pass
+        if (md->res_np == 2) e = md->f32 ? launch(k_resident<true, 2, 2>) : launch(k_resident<false, 2, 2>);
+        else if (md->res_bs > 512) e = md->f32 ? launch(k_resident<true, 1, 2>) : launch(k_resident<false, 1, 2>);
+        else e = md->f32 ? launch(k_resident<true, 1, 4>) : launch(k_resident<false, 1, 4>);
+        if (e != hipSuccess) return e;
+        // the kernel's own schedule: a rebuild before the step that finds the lists K steps old
+        if (a.nsteps == 0) {
+            if (md->since_rebuild >= md->K) md->since_rebuild = 0;
+            break;
+        }
+        const long long end = (long long)std::min(md->since_rebuild, md->K) + a.nsteps;
+        md->since_rebuild = (int)((end - 1) % md->K + 1);
+        md->vel_full = false;
+        md->steps_done += a.nsteps;
+        if (md->cg_on) {
+            md->events += (md->cg_t % md->s_cg + a.nsteps) / md->s_cg;
+            md->cg_t += a.nsteps;
+        }
+        count -= a.nsteps;
+    } while (count > 0);
+    return e;
+}
+
 // What distinguishes the kernel sequence of a unit (rebuild + K steps) starting
 // now: the offsets of its coarse-graining events.  With s_cg <= K they follow
 // from cg_t mod s_cg; with s_cg > K a unit holds at most one event, after
@@ -2732,7 +3311,54 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
             if (fs != 2 && tiles(3, kPairTarget3)) md->three_step = true;
             else if (!tiles(2, kPairTarget)) md->two_step = false;
         }
+        md->spl = md->three_step ? 3 : (md->two_step ? 2 : 1);
         if (!md->two_step) md->npt = 0;
+    }
+    double mean_max = 0.0;
+    if (md->variant == 3) {
+        // list capacity: twice the mean neighbour count of the densest replica plus 16
+        for (int r = 0; r < n_rep; ++r) {
+            const RepDev& d = md->reps[r].d;
+            mean_max = std::max(mean_max, 3.14159265358979 * d.w * d.w * (double)d.n / (d.L * d.L));
+        }
+        md->maxnb = std::min(248, ((int)std::ceil(2.0 * mean_max + 16.0) + 7) / 8 * 8);
+    }
+    if (md->variant == 3 && p[0].fuse_steps == 0) {
+        // A block per replica where every replica fits one: a single replica of
+        // 2048 particles takes 2.5 us per step that way and 2.5 us on tiles over
+        // several compute units (1500 dense ones 7.0 and 7.1 us), smaller ones
+        // and batches less (256 x 2048: 2.9 against 9.0 us).
+        int nmax = 0, cmax = 0;
+        for (int r = 0; r < n_rep; ++r) {
+            nmax = std::max(nmax, md->reps[r].d.n);
+            cmax = std::max(cmax, std::min(md->reps[r].d.nc, 1000) * std::min(md->reps[r].d.nc, 1000));
+        }
+        if (nmax <= kResMax) {
+            md->res_bs = std::min(kResBS, (nmax + 63) / 64 * 64);
+            md->res_np = (nmax + md->res_bs - 1) / md->res_bs;
+            md->res_cap = (nmax + 63) / 64 * 64;
+            md->res_cells = cmax;
+            // list rows: all, or what LDS leaves, if that holds nearly every list (the mean and four deviations)
+            const size_t fixed = 2 * sizeof(double2) * md->res_cap + 2 * (size_t)((cmax + 8) / 8 * 8);
+            const size_t scratch = 4 * ((size_t)cmax + md->res_cap);  // of a rebuild, in the lists' place
+            const size_t room = fixed + scratch <= (size_t)kResLds ? kResLds - fixed : 0;
+            md->res_rows = std::min(md->maxnb, (int)(room / (2 * (size_t)md->res_cap)) / 4 * 4);
+            md->res_lds = fixed + std::max((size_t)md->res_rows * md->res_cap * 2, scratch);
+            md->resident = md->res_rows >= std::max(8.0, std::min((double)md->maxnb, mean_max + 4.0 * std::sqrt(mean_max)));
+        }
+        if (md->resident) {
+            // its lists are those of the one-step kernel, its cells those of every kernel
+            md->two_step = md->three_step = false;
+            md->npt = 0;
+            auto allow = [&](const void* k) { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kResLds); };
+            const void* kernels[] = {(const void*)k_resident<true, 2, 2>, (const void*)k_resident<false, 2, 2>,
+                                     (const void*)k_resident<true, 1, 2>, (const void*)k_resident<false, 1, 2>,
+                                     (const void*)k_resident<true, 1, 4>, (const void*)k_resident<false, 1, 4>};
+            bool allowed = true;
+            for (const void* k : kernels) allowed = allowed && allow(k) == hipSuccess;
+            if (!allowed)
+                return destroy_on_fail(md, fail(MDLG_EHIP, "lj_md_init: LDS size refused"));
+        }
     }
 
     auto A = [&](hipError_t e) { return e == hipSuccess; };
@@ -2751,13 +3377,6 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
          A(dalloc(&md->d_mpart, part_tiles * MDLG_NMOMENTS)) && A(dalloc(&md->d_event_k, 1)) &&
          A(hipStreamCreateWithFlags(&md->cap, hipStreamNonBlocking));
     if (ok && md->variant == 3) {
-        // list capacity: twice the mean neighbour count of the densest replica plus 16
-        double mean_max = 0.0;
-        for (int r = 0; r < n_rep; ++r) {
-            const RepDev& d = md->reps[r].d;
-            mean_max = std::max(mean_max, 3.14159265358979 * d.w * d.w * (double)d.n / (d.L * d.L));
-        }
-        md->maxnb = std::min(248, ((int)std::ceil(2.0 * mean_max + 16.0) + 7) / 8 * 8);
         static_assert(248 % kListU == 0 && 248 % kListUOne == 0 && kListPre <= 16, "list rows are read in whole passes");
         for (int r = 0; r < n_rep; ++r) {
             // list entries are 16-bit slot offsets: a neighbour lies within about
@@ -2916,6 +3535,10 @@ extern "C" mdlg_status lj_md_step(lj_md* md, int64_t nsteps, void* stream) {
     if (md->broken) return fail(MDLG_EINVAL, "lj_md_step: handle is unusable after a device fault");
     if (nsteps < 0) return fail(MDLG_EINVAL, "lj_md_step: nsteps must be >= 0");
     hipStream_t st = (hipStream_t)stream;
+    if (md->resident) {
+        if (nsteps > 0) MDLG_HIP(run_resident(md, st, nsteps));
+        return MDLG_OK;
+    }
     while (nsteps > 0) {
         const long long n = eager_len(md, nsteps);
         if (n == 0) {
@@ -2954,6 +3577,72 @@ mdlg_status capture(lj_md* md, F fn, hipGraphExec_t* out) {
 
 }  // namespace
 
+namespace {
+
+// lj_md_step_timed of a resident handle: a sampled interval as three launches
+// (the rebuild, the steps before its first event, the rest) with events between
+// them, the intervals in between as one.
+mdlg_status step_timed_resident(lj_md* md, int64_t nunits, int32_t sample_every, double* ms_out, int32_t* n_out,
+                                hipStream_t st) {
+    if (md->vel_full) MDLG_HIP(run_resident(md, st, 1));
+    struct Unit {
+        hipEvent_t ev[4];
+        int lead, events;
+    };
+    std::vector<Unit> units;
+    hipError_t e = hipSuccess;
+    for (int64_t u = 0; u < nunits && e == hipSuccess; ++u) {
+        md->since_rebuild = md->K;  // an interval starts with its rebuild
+        if (u % sample_every != 0) {
+            const int64_t run = std::min<int64_t>(sample_every - u % sample_every, nunits - u);
+            e = run_resident(md, st, run * md->K);
+            u += run - 1;
+            continue;
+        }
+        Unit w{{nullptr, nullptr, nullptr, nullptr}, md->K, 0};
+        if (md->cg_on) w.lead = (int)std::min<long long>(md->K, md->s_cg - md->cg_t % md->s_cg - 1);
+        for (int q = 0; q < 4 && e == hipSuccess; ++q) e = hipEventCreate(&w.ev[q]);
+        units.push_back(w);
+        if (e == hipSuccess) e = hipEventRecord(w.ev[0], st);
+        if (e == hipSuccess) e = run_resident(md, st, 0);
+        if (e == hipSuccess) e = hipEventRecord(w.ev[1], st);
+        if (e == hipSuccess && w.lead > 0) e = run_resident(md, st, w.lead);
+        if (e == hipSuccess) e = hipEventRecord(w.ev[2], st);
+        const long long ev0 = md->events;
+        if (e == hipSuccess && w.lead < md->K) e = run_resident(md, st, md->K - w.lead);
+        if (e == hipSuccess) e = hipEventRecord(w.ev[3], st);
+        units.back().events = (int)(md->events - ev0);
+    }
+    const hipError_t es = hipStreamSynchronize(st);
+    if (e == hipSuccess) e = es;
+    double sum[3] = {0.0, 0.0, 0.0};
+    long long n[3] = {0, 0, 0};
+    for (size_t k = units.size() > 1 ? 1 : 0; k < units.size() && e == hipSuccess; ++k) {  // the first one warms up
+        const Unit& w = units[k];
+        float t[3] = {0, 0, 0};
+        for (int q = 0; q < 3; ++q) (void)hipEventElapsedTime(&t[q], w.ev[q], w.ev[q + 1]);
+        sum[2] += t[0];
+        n[2] += 1;
+        sum[0] += t[1];
+        n[0] += w.lead;
+        if (w.events > 0) {
+            sum[1] += t[2];
+            n[1] += w.events;
+        }
+    }
+    for (const Unit& w : units)
+        for (hipEvent_t x : w.ev)
+            if (x) (void)hipEventDestroy(x);
+    if (e != hipSuccess) return fail(MDLG_EHIP, std::string("lj_md_step_timed: ") + hipGetErrorString(e));
+    for (int q = 0; q < 3; ++q) {
+        ms_out[q] = n[q] ? sum[q] / (double)n[q] : 0.0;
+        if (n_out) n_out[q] = (int32_t)n[q];
+    }
+    return MDLG_OK;
+}
+
+}  // namespace
+
 extern "C" mdlg_status lj_md_step_timed(lj_md* md, int64_t nunits, int32_t sample_every, double* ms_out,
                                         int32_t* n_out, void* stream) {
     if (!md || !ms_out) return fail(MDLG_EINVAL, "lj_md_step_timed: NULL argument");
@@ -2964,6 +3653,7 @@ extern "C" mdlg_status lj_md_step_timed(lj_md* md, int64_t nunits, int32_t sampl
     if (!md->use_graphs && sample_every > 1)
         return fail(MDLG_EINVAL, "lj_md_step_timed: sample_every > 1 needs graph replay");
     hipStream_t st = (hipStream_t)stream;
+    if (md->resident) return step_timed_resident(md, nunits, sample_every, ms_out, n_out, st);
     // direct launches up to the first interval aligned with the coarse steps
     while (md->vel_full || steps_to_alignment(md) > 0) {
         const long long n = md->vel_full ? 1 : steps_to_alignment(md);
@@ -3272,7 +3962,7 @@ extern "C" mdlg_status lj_md_info(const lj_md* md, lj_md_info_t* info) {
     info->cells_per_side = md->reps[0].d.nc;
     info->block_size = md->BS;
     info->cell_width = md->reps[0].d.w;
-    info->steps_per_launch = md->three_step ? 3 : (md->two_step ? 2 : 1);
+    info->steps_per_launch = md->spl;
     info->reserved = 0;
     return MDLG_OK;
 }

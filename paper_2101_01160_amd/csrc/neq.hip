@@ -299,7 +299,7 @@ extern "C" mdlg_status mdlg_neq_mdlg(int64_t n_total, double box_l, int32_t lx, 
         }
         const size_t lds = sizeof(unsigned) * (size_t)ni * lx * lx;
         if (lds > 32 * 1024)
-            MDLG_HIP(hipFuncSetAttribute((const void*)k_neq_event, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            MDLG_HIP(hipFuncSetAttribute((const void*)k_neq_event, hipFuncAttributeMaxDynamicSharedMemorySize, kNeqLdsInts * 4));
         hipLaunchKernelGGL(k_neq_event, dim3((unsigned)(nev * parts)), dim3(kNeqEventBS), lds, st, (const double2*)pos,
                            (const int2*)img, (long long)n_total, lx, (double)lx / box_l, ni, parts, (unsigned*)f_sum,
                            (unsigned long long*)overflow);

@@ -227,7 +227,8 @@ extern "C" mdlg_status mdlg_vacf(int32_t n_rep, const int64_t* offsets, int32_t 
     if (e == hipSuccess && staged) {
         auto launch = [&](auto kernel) {
             hipError_t le = hipSuccess;
-            if (lds > 32 * 1024) le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (lds > 32 * 1024)
+                le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kVacfLds - (int)red_of(pt));
             if (le != hipSuccess) return le;
             hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kVacfLdsBS), lds, st, (const double2*)vel, n_tot, n_snap,
                                d_blocks, d_lags, n_lag, (int)nb, part);

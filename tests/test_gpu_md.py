@@ -645,3 +645,66 @@ def test_several_intervals_per_graph_equal_one_at_a_time(s_cg):
         sysm.close()
     for x, y in zip(out[0], out[1]):
         assert np.array_equal(x, y)
+
+
+@pytest.mark.parametrize("sizes,phi,kT,kw", [
+    ([40], 0.1, 20.0, {}), ([64], 0.2, 5.0, {}), ([65], 0.2, 5.0, {"rebuild_every": 1}),
+    ([1023], 0.0784, 20.0, {"rebuild_every": 7}), ([1024], 0.4, 20.0, {}), ([1025], 0.3, 5.0, {"force_bits": 32}),
+    ([2048], 0.0784, 20.0, {}), ([1500, 40, 700, 1999], 0.15, 10.0, {"rebuild_every": 11}),
+    ([1100], 0.4, 5.0, {}), ([961 + 1024], "cluster", 0.1, {"rebuild_every": 9}),
+])
+def test_block_per_replica_equals_one_step(sizes, phi, kT, kw):
+    """Replicas that fit one block (the default up to 2048 particles) against one step per launch: with the lists
+    rebuilt at the same steps, the same states and counts bit for bit, whatever the calls; the moments to their
+    rounding, and bit for bit between splits of the run."""
+    import torch
+
+    import paper_2101_01160_amd as m
+    print(f"block per replica {sizes} phi={phi} {kw}", flush=True)
+    if phi == "cluster":  # lists longer than LDS holds: a lattice at 1.05 beside a dilute one
+        (n,), g, h = sizes, 150.0 + 1.05 * np.arange(31), 2.0 + 3.0 * np.arange(32)
+        pts = np.concatenate([np.stack(np.meshgrid(x, x), axis=-1).reshape(-1, 2) for x in (g, h)])
+        states = [(pts, mi.maxwell_velocities(n, kT, np.random.default_rng(2)), 300.0)]
+    else:
+        states = [mi.initial_state(n, phi, kT, 70 + k) for k, n in enumerate(sizes)]
+    pos, vel = (np.concatenate([s[k] for s in states]) for k in (0, 1))
+    out = []
+    for fuse, calls in ((1, [1] * 61), (0, [61]), (0, [1, 2, 0, 17, 3, 38])):
+        b = m.LJSystem(_cuda(pos), _cuda(vel), params=[m.lj_params(n, s[2], fuse_steps=fuse, **kw)
+                                                       for n, s in zip(sizes, states)])
+        acc = b.attach_cg([max(7, int(s[2] / 2.0)) for s in states], 5, u=(0.1, -0.3), cell_acc=True)
+        for c in calls:
+            b.step(c)
+        b.check()
+        assert acc.events == 12 and b.info()["steps_done"] == 61
+        out.append([_np(t) for t in b.state()] + [_np(b.forces()), _np(acc.counts), _np(acc.cell_acc), _np(acc.moments)])
+        b.close()
+    for x, y, z in zip(*out):
+        assert np.array_equal(y, z)
+        if x is not out[0][6]:
+            assert np.array_equal(x, y)
+    for r in range(len(sizes)):
+        assert_moments_close(out[1][6][r], out[0][6][r])
+    torch.cuda.synchronize()
+
+
+def test_block_per_replica_reports_drift_and_times_steps():
+    pos0, vel0, L = mi.initial_state(900, 0.0784, 20.0, 4)
+    sysm = gpu_system(pos0, vel0, L)
+    acc = sysm.attach_cg(20, 25)
+    ms, cnt = sysm.step_timed(9, 3)
+    K = sysm.info()["rebuild_every"]
+    assert (ms > 0).all() and sysm.info()["steps_done"] == 9 * K + 1 and cnt[2] == 2
+    sysm.step(25 - (9 * K + 1) % 25)
+    oacc = omd.CGAccum(20)
+    steps = sysm.info()["steps_done"]
+    omd.md_run(pos0, vel0, np.zeros((900, 2), np.int64), L, steps, cg=oacc, s_cg=25)
+    assert acc.events == steps // 25 and np.array_equal(_np(acc.counts)[0], oacc.counts)
+    sysm.check()
+    sysm.close()
+    import paper_2101_01160_amd as m
+    sysm = gpu_system(pos0, vel0, L, rebuild_every=1000)
+    with pytest.raises(m.MDLGError, match="skin"):
+        sysm.step(1500)
+        sysm.check()
+    sysm.close()
