@@ -10,12 +10,17 @@
 // n_bin/2) h), k = floor(delta * (1/h) + n_bin/2) rounded once per operation.
 //
 // The work is HBM-bound: 48 bytes of snapshot data per particle pair and two
-// LDS counter increments.  A block owns 256 particles of one replica, one lag
-// and one chunk of snapshot pairs; its two per-axis histograms sit in LDS
-// (32-bit, at most 256 x 2^24 counts a bin) and are added to the int64 output
-// with one global atomic per non-empty bin.
+// LDS counter increments.  A block owns one replica, one lag and a share of its
+// work items (512 particles of one snapshot pair); its per-axis histograms sit
+// in LDS (32-bit, in a few copies so that the lanes of a wave seldom meet in a
+// bin) and are added to the int64 output with one global atomic per non-empty
+// bin.  About 512 blocks in all keep those few: with a block per 256 particles
+// and chunk of pairs the 890,000 global atomics of 4 x 99,856 particles, 8 pairs
+// and 96 bins took most of 33 us; 17.7 us here (20.6 us with 1024 blocks of half
+// the threads).  The tables of a call travel as kernel arguments: no allocation
+// and no copy, which with the wait for them took half of its 81 us (40 us now).
+#include <algorithm>
 #include <cmath>
-#include <cstring>
 #include <vector>
 
 #include "mdlg_internal.h"
@@ -23,28 +28,25 @@
 namespace mdlg {
 namespace {
 
-constexpr int kHistBS = 256;
+constexpr int kHistBS = 512;
 constexpr int kHistMaxLags = 64;
 constexpr int kHistMaxSnap = 1 << 24;
-constexpr int kHistTargetBlocks = 4096;  // enough waves in flight to cover HBM latency
-
-struct HistBlock {
-    long long start;  // first particle (index into n_tot)
-    int count;        // particles in this block (<= kHistBS)
-    int rep;          // replica
-};
+constexpr int kHistTargetBlocks = 512;   // blocks of a launch aimed at: two per compute unit
+constexpr int kHistReps = 32;            // replicas of one launch
+constexpr int kHistU = 4;                // work items of a thread in flight
+constexpr int kHistCopyLds = 16 * 1024;  // LDS that copies of the histograms may take
 
 struct HistArgs {
     const double2* __restrict__ pos;
     const int2* __restrict__ img;
     long long n_tot;
-    int n_snap, n_bin, n_lag, n_chunk;
+    int n_snap, n_bin, n_lag, copies;
     double half;                               // n_bin / 2
-    const HistBlock* __restrict__ blocks;
-    const double* __restrict__ box;            // [n_rep]
-    const int* __restrict__ lags;              // [n_lag]
-    const double* __restrict__ inv_h;          // [n_lag] 1 / h
-    unsigned long long* __restrict__ hist;     // [n_rep][n_lag][2][n_bin + 2]
+    unsigned long long* __restrict__ hist;     // [replicas of the launch][n_lag][2][n_bin + 2]
+    long long offset[kHistReps + 1];
+    double box[kHistReps];
+    int lags[kHistMaxLags];
+    double inv_h[kHistMaxLags];                // 1 / h
 };
 
 __device__ __forceinline__ double box_delta(double xc, double xp, int di, double L) {
@@ -63,41 +65,58 @@ __device__ __forceinline__ int disp_bin(double d, double inv_h, double half, int
 }
 
 __global__ __launch_bounds__(kHistBS) void k_disp_hist(HistArgs a) {
-    extern __shared__ unsigned hl[];  // [2][n_bin + 2]
+    extern __shared__ unsigned hl[];  // [2 (n_bin + 2)][copies]
     const int tid = threadIdx.x;
     const int nb2 = 2 * (a.n_bin + 2);
-    for (int i = tid; i < nb2; i += kHistBS) hl[i] = 0u;
-    __syncthreads();
-    const HistBlock blk = a.blocks[blockIdx.x];
-    const int s = blockIdx.y;
-    const int l = a.lags[s];
-    // this block's share of the pairs p = l .. n_snap - 1
+    const int s = blockIdx.y, r = blockIdx.z, l = a.lags[s];
+    const long long j0 = a.offset[r];
+    const long long n = a.offset[r + 1] - j0;
     const int npair = a.n_snap - l;
-    const int span = (npair + a.n_chunk - 1) / a.n_chunk;
-    const int p0 = l + (int)blockIdx.z * span;
-    const int p1 = min(a.n_snap, p0 + span);
-    if (tid < blk.count && p0 < p1) {
-        const double L = a.box[blk.rep];
-        const double inv = a.inv_h[s];
-        const long long j = blk.start + tid;
-        unsigned* hx = hl;
-        unsigned* hy = hl + a.n_bin + 2;
-#pragma unroll 4
-        for (int p = p0; p < p1; ++p) {
-            const double2 xc = a.pos[(long long)p * a.n_tot + j];
-            const double2 xp = a.pos[(long long)(p - l) * a.n_tot + j];
-            const int2 ic = a.img[(long long)p * a.n_tot + j];
-            const int2 ip = a.img[(long long)(p - l) * a.n_tot + j];
-            const int bx = disp_bin(box_delta(xc.x, xp.x, ic.x - ip.x, L), inv, a.half, a.n_bin);
-            const int by = disp_bin(box_delta(xc.y, xp.y, ic.y - ip.y, L), inv, a.half, a.n_bin);
-            atomicAdd(hx + bx, 1u);
-            atomicAdd(hy + by, 1u);
+    // this block's share of the items: group i / npair of kHistBS particles, pair i % npair
+    const long long items = (n + kHistBS - 1) / kHistBS * npair;
+    const long long i0 = items * blockIdx.x / gridDim.x, i1 = items * (blockIdx.x + 1LL) / gridDim.x;
+    if (i0 >= i1) return;  // uniform over the block
+    for (int i = tid; i < nb2 * a.copies; i += kHistBS) hl[i] = 0u;
+    __syncthreads();
+    const double L = a.box[r], inv = a.inv_h[s];
+    unsigned* hx = hl + tid % a.copies;
+    unsigned* hy = hx + (a.n_bin + 2) * a.copies;
+    long long g = i0 / npair;
+    int q = (int)(i0 % npair);
+    for (long long i = i0; i < i1; i += kHistU) {
+        double2 xc[kHistU], xp[kHistU];
+        int2 ic[kHistU], ip[kHistU];
+        bool on[kHistU];
+#pragma unroll
+        for (int u = 0; u < kHistU; ++u) {
+            const long long j = g * kHistBS + tid;
+            on[u] = i + u < i1 && j < n;
+            if (on[u]) {
+                const long long at = (long long)q * a.n_tot + j0 + j, to = at + l * a.n_tot;
+                xp[u] = a.pos[at];
+                xc[u] = a.pos[to];
+                ip[u] = a.img[at];
+                ic[u] = a.img[to];
+            }
+            if (++q == npair) {
+                q = 0;
+                ++g;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kHistU; ++u) {
+            if (!on[u]) continue;
+            const int bx = disp_bin(box_delta(xc[u].x, xp[u].x, ic[u].x - ip[u].x, L), inv, a.half, a.n_bin);
+            const int by = disp_bin(box_delta(xc[u].y, xp[u].y, ic[u].y - ip[u].y, L), inv, a.half, a.n_bin);
+            atomicAdd(hx + bx * a.copies, 1u);
+            atomicAdd(hy + by * a.copies, 1u);
         }
     }
     __syncthreads();
-    unsigned long long* out = a.hist + ((long long)blk.rep * a.n_lag + s) * nb2;
+    unsigned long long* out = a.hist + ((long long)r * a.n_lag + s) * nb2;
     for (int i = tid; i < nb2; i += kHistBS) {
-        const unsigned c = hl[i];
+        unsigned c = 0u;
+        for (int k = 0; k < a.copies; ++k) c += hl[i * a.copies + k];
         if (c) atomicAdd(out + i, (unsigned long long)c);
     }
 }
@@ -130,35 +149,19 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
         lmin = lags[s] < lmin ? lags[s] : lmin;
     }
     if (offsets[0] != 0) return fail(MDLG_EINVAL, std::string(who) + "offsets[0] must be 0");
-    std::vector<HistBlock> blocks;
+    long long n_max = 0, groups = 0;
     for (int r = 0; r < n_rep; ++r) {
         const long long n = offsets[r + 1] - offsets[r];
         if (n < 0) return fail(MDLG_EINVAL, std::string(who) + "offsets must be non-decreasing");
         if (!(box_l[r] > 0.0) || !std::isfinite(box_l[r])) return fail(MDLG_EINVAL, std::string(who) + "box_l must be > 0");
-        for (long long s0 = 0; s0 < n; s0 += kHistBS)
-            blocks.push_back({offsets[r] + s0, (int)(n - s0 < kHistBS ? n - s0 : kHistBS), r});
+        n_max = std::max(n_max, n);
+        groups += (n + 255) / 256;
     }
-    if (blocks.empty()) return MDLG_OK;  // no particles, nothing to add
-    const long long nb = (long long)blocks.size();
-    if (nb >= (1LL << 24)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
-    // split the snapshot pairs so that the grid holds enough blocks
-    long long want = (kHistTargetBlocks + nb * n_lag - 1) / (nb * n_lag);
-    const int n_chunk = (int)std::max(1LL, std::min<long long>({want, (long long)(n_snap - lmin), 65535LL}));
+    if (n_max == 0) return MDLG_OK;  // no particles, nothing to add
+    if (groups >= (1LL << 24))
+        return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
     hipStream_t st = (hipStream_t)stream;
-    const size_t bytes_blocks = sizeof(HistBlock) * blocks.size();
-    const size_t off_box = (bytes_blocks + 255) / 256 * 256;
-    const size_t off_inv = off_box + sizeof(double) * n_rep;
-    const size_t off_lags = off_inv + sizeof(double) * n_lag;
-    const size_t total = off_lags + sizeof(int) * n_lag;
-    std::vector<unsigned char> host(total, 0);
-    std::memcpy(host.data(), blocks.data(), bytes_blocks);
-    std::memcpy(host.data() + off_box, box_l, sizeof(double) * n_rep);
-    std::memcpy(host.data() + off_inv, inv_h.data(), sizeof(double) * n_lag);
-    std::memcpy(host.data() + off_lags, lags, sizeof(int) * n_lag);
-    unsigned char* dev = nullptr;
-    MDLG_HIP(hipMallocAsync((void**)&dev, total, st));
-    hipError_t e = hipMemcpyAsync(dev, host.data(), total, hipMemcpyHostToDevice, st);
-    const bool copied = e == hipSuccess;
+    const int nb2 = 2 * (n_bin + 2);
     HistArgs a{};
     a.pos = (const double2*)pos;
     a.img = (const int2*)img;
@@ -166,28 +169,29 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
     a.n_snap = n_snap;
     a.n_bin = n_bin;
     a.n_lag = n_lag;
-    a.n_chunk = n_chunk;
     a.half = 0.5 * (double)n_bin;
-    a.blocks = (const HistBlock*)dev;
-    a.box = (const double*)(dev + off_box);
-    a.inv_h = (const double*)(dev + off_inv);
-    a.lags = (const int*)(dev + off_lags);
-    a.hist = (unsigned long long*)hist;
-    const size_t lds = sizeof(unsigned) * 2 * ((size_t)n_bin + 2);
-    if (e == hipSuccess && lds > 64 * 1024)
-        e = hipFuncSetAttribute((const void*)k_disp_hist, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e == hipSuccess) {
-        hipLaunchKernelGGL(k_disp_hist, dim3((unsigned)nb, (unsigned)n_lag, (unsigned)n_chunk), dim3(kHistBS), lds,
-                           st, a);
+    a.copies = 1;
+    while (a.copies < 8 && 2 * a.copies * nb2 * (int)sizeof(unsigned) <= kHistCopyLds) a.copies *= 2;
+    for (int s = 0; s < n_lag; ++s) {
+        a.lags[s] = lags[s];
+        a.inv_h[s] = inv_h[s];
+    }
+    const size_t lds = sizeof(unsigned) * (size_t)nb2 * a.copies;  // at most 32 KB
+    hipError_t e = hipSuccess;
+    for (int r0 = 0; r0 < n_rep && e == hipSuccess; r0 += kHistReps) {
+        const int nr = std::min(kHistReps, n_rep - r0);
+        for (int r = 0; r <= nr; ++r) a.offset[r] = offsets[r0 + r];
+        for (int r = 0; r < nr; ++r) a.box[r] = box_l[r0 + r];
+        a.hist = (unsigned long long*)hist + (size_t)r0 * n_lag * nb2;
+        // shares: about kHistTargetBlocks blocks, none without work, none with 2^24 items (2^32 counts)
+        const long long items = (n_max + kHistBS - 1) / kHistBS * (n_snap - lmin);
+        const long long want = std::max((long long)kHistTargetBlocks / (nr * n_lag), items >> 23);
+        const unsigned nx = (unsigned)std::max(1LL, std::min(want, items));
+        hipLaunchKernelGGL(k_disp_hist, dim3(nx, (unsigned)n_lag, (unsigned)nr), dim3(kHistBS), lds, st, a);
         e = hipGetLastError();
     }
-    // the host table must outlive the copy: wait before it goes out of scope
-    if (copied) {
-        const hipError_t es = hipStreamSynchronize(st);
-        if (e == hipSuccess) e = es;
-    }
-    hipError_t e2 = hipFreeAsync(dev, st);
+    const hipError_t es = hipStreamSynchronize(st);
     MDLG_HIP(e);
-    MDLG_HIP(e2);
+    MDLG_HIP(es);
     return MDLG_OK;
 }

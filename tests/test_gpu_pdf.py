@@ -68,6 +68,17 @@ def test_ragged_batch_matches_oracle():
             assert (got[r, s].sum(axis=1) == 2 * n * (P - lag)).all()
 
 
+@pytest.mark.parametrize("n_rep,n_bin", [(33, 24), (70, 1021)])
+def test_several_launches_and_shares(n_rep, n_bin):
+    """More replicas than one launch takes, ragged around whole work items, some empty; one and several histogram copies."""
+    sizes = [(511, 512, 513, 0, 1, 1537)[r % 6] for r in range(n_rep)]
+    xs, imgs, off = batch([(n, 10.0 + r, 0.8) for r, n in enumerate(sizes)], 5, seed=9)
+    box = [10.0 + r for r in range(n_rep)]
+    lags, h = [1, 3], [8.0 / n_bin, 12.0 / n_bin]
+    got = gpu_hist(off, box, xs, imgs, lags, h, n_bin)
+    assert np.array_equal(got, omd.displacement_hist_series(off, box, xs, imgs, lags, h, n_bin))
+
+
 @pytest.mark.parametrize("n_bin", [1, 2, 4094])
 def test_bin_count_extremes(n_bin):
     specs = [(700, 20.0, 1.0), (129, 33.0, 0.4)]
