@@ -105,6 +105,24 @@ def test_gradient_matches_reference(B):
         assert rel <= 3e-2, name
 
 
+@pytest.mark.parametrize("B", [1, 15, 17, 31, 33, 257, 1025, 4096, 4129])
+def test_gradient_at_batch_edges(B):
+    """Batches around the samples of a block (16), of a k step (32) and of the splits of the weight gradients, in a
+    handle with room for more (whose buffers hold an earlier batch): the FP64 reference to the bounds of bf16 products."""
+    theta = params(2)
+    net = make(theta, 5000)
+    net.gradient(_t(inputs(1, 5000)), _t(targets(1, 5000)))
+    X, R = inputs(12, B), targets(12, B)
+    loss, grad = net.gradient(_t(X), _t(R))
+    grad = grad.cpu().numpy().astype(np.float64)
+    assert float(loss.cpu()[0]) == pytest.approx(om.loss(theta, X, R), rel=1e-2)
+    ref = om.grad(theta, X, R)
+    for name, a, b in BLOCKS:
+        g, r = grad[a:b], ref[a:b]
+        assert g @ r >= 0.999 * np.linalg.norm(g) * np.linalg.norm(r), name
+        assert np.linalg.norm(g - r) <= 3e-2 * np.linalg.norm(r), name
+
+
 def test_first_adam_step_is_lr_times_sign():
     import torch
     B, lr = 128, 1e-3
