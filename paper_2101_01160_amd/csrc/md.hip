@@ -83,8 +83,10 @@ struct StepArgs {
     int nrep;
     int nslots;     // total slots: loads of the prologue are clamped below it
     int stage_max;  // tile kernel: largest staged particle count (<= its LDS capacity)
-    const short* __restrict__ nbl;          // neighbour lists [maxnb][S]: slot offsets
+    const short* __restrict__ nbl;          // neighbour lists (see k_nlist_build)
     const unsigned char* __restrict__ nbc;  // neighbour counts [S]
+    const int* __restrict__ trange;         // [slot tiles][kRangeInts]: what a block of the one-step kernel stages
+    const unsigned short* __restrict__ lane_slot;  // [S]: slot within the tile of each lane of its force pass
     // two- and three-step launches
     double2* __restrict__ vout;                 // velocities written by the fused kernels
     const int* __restrict__ plist;              // [tiles][kPairCap]: staged slots, owned then ring by ring
@@ -722,6 +724,91 @@ __device__ __forceinline__ bool within_list_range(double dx, double dy, double r
     return r2 < rl2;
 }
 
+constexpr int kListU = 2;              // fused kernels (lists ordered by length within a tile)
+constexpr int kListPre = 4 * kListU;  // rows loaded ahead for a thread's first particle (maxnb >= 16)
+constexpr int kListPreEvent = 2 * kListU;  // the same in the event and binning launches
+
+// What a block of the one-step kernel stages in LDS: the particles of every
+// cell next to one of its own.  A tile of consecutive slots covers consecutive
+// cells cA .. cB of the row-major order, so these are three runs of consecutive
+// cells, [cA + d nc - 1, cB + d nc + 1] for d = -1, 0, 1, with cell numbers
+// taken modulo nc^2 (the periodic edge in y).  Across the edge in x a cell's
+// neighbours lie in the same runs but for two: the one above and to the left of
+// a row's first cell, 2 nc - 1 on, and the one below and to the right of its
+// last, 2 nc - 1 back, which make the fourth and fifth run.  Runs that meet are one run; one that closes on
+// itself is the whole replica.  Particles are staged in virtual slot order, slots
+// taken modulo n.
+struct TileRanges {
+    int lo[5], hi[5];    // cells of each run (lo > hi: none)
+    int start[5];        // virtual slot of its first particle
+    int base[6];         // its first staged index; the total
+    int own;             // staged index of the tile's first slot
+    int whole;           // the first run is the whole replica: cells modulo nc^2
+    int pad;
+};
+constexpr int kRangeInts = sizeof(TileRanges) / sizeof(int);
+constexpr int kStageMul = 4;  // staged particles per thread at most; a tile with more reads global memory
+constexpr int kPassOne = 4;   // list entries per pass of the one-step kernel: one 8-byte word
+constexpr int kPreOne = 4;    // passes whose words are loaded ahead (lists have room for 16 entries at least)
+constexpr int kPreShort = 2;  // the same where positions are not staged
+constexpr double kStageMean = 7.0;  // mean list length from which the one-step kernel stages positions: see k_step_nlist
+
+// Particles in the cells before virtual cell v of a replica (-nc^2 <= v <= 2 nc^2).
+__device__ __forceinline__ int slots_before(const int* __restrict__ cs, const RepDev& R, int v) {
+    const int c2 = R.nc * R.nc;
+    return v < 0 ? cs[R.cell0 + v + c2] - R.slot0 - R.n
+                 : (v >= c2 ? cs[R.cell0 + v - c2] - R.slot0 + R.n : cs[R.cell0 + v] - R.slot0);
+}
+
+__global__ void k_tile_ranges(const int* __restrict__ cs, const RepDev* __restrict__ reps, const int* __restrict__ tile_rep,
+                              const int* __restrict__ cellof, int BSt, int ntile, int* __restrict__ out) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= ntile) return;
+    const RepDev& R = reps[tile_rep[t]];
+    const int nc = R.nc, c2 = nc * nc, s0 = t * BSt;
+    TileRanges T{};
+    for (int r = 0; r < 5; ++r) T.hi[r] = -1;
+    if (s0 - R.slot0 < R.n) {
+        const int s1 = min(s0 + BSt, R.slot0 + R.n) - 1;
+        const int cA = cellof[s0] - R.cell0, cB = cellof[s1] - R.cell0;
+        if (cB - cA + 2 * nc + 3 >= c2) {
+            T.hi[0] = c2 - 1;
+            T.whole = 1;
+        } else if (cB + 1 >= cA + nc - 1) {
+            T.lo[0] = cA - nc - 1;
+            T.hi[0] = cB + nc + 1;
+        } else {
+            for (int d = 0; d < 3; ++d) {
+                T.lo[d] = cA + (d - 1) * nc - 1;
+                T.hi[d] = cB + (d - 1) * nc + 1;
+            }
+        }
+        if (!T.whole) {
+            const int f0 = (cA + nc - 1) / nc * nc, f1 = cB / nc * nc;                        // rows' first cells
+            const int l0 = cA / nc * nc + nc - 1, l1 = (cB + 1) / nc * nc - 1;                // and last ones
+            if (f0 <= f1) {
+                T.lo[3] = f0 + 2 * nc - 1;
+                T.hi[3] = f1 + 2 * nc - 1;
+            }
+            if (l0 <= l1) {
+                T.lo[4] = l0 - 2 * nc + 1;
+                T.hi[4] = l1 - 2 * nc + 1;
+            }
+        }
+        int at = 0;
+        for (int r = 0; r < 5; ++r) {
+            T.base[r] = at;
+            if (T.lo[r] > T.hi[r]) continue;
+            T.start[r] = slots_before(cs, R, T.lo[r]);
+            at += slots_before(cs, R, T.hi[r] + 1) - T.start[r];
+        }
+        T.base[5] = at;
+        const int own = T.whole || T.lo[1] > T.hi[1] ? 0 : 1;
+        T.own = T.base[own] + (s0 - R.slot0) - T.start[own];
+    }
+    reinterpret_cast<TileRanges*>(out)[t] = T;
+}
+
 // Neighbour lists: for every slot, the slots within rc + skin (the cell width)
 // of it, found through the 3 x 3 cells right after the cell-list rebuild.
 // Layout nbl[j * S + s] (consecutive slots consecutive in memory for each j).
@@ -733,12 +820,23 @@ __device__ __forceinline__ bool within_list_range(double dx, double dy, double r
 // relative to the particle's, (oy + 1) 3 + (ox + 1) in bits 12-15, and its
 // index within that cell in bits 0-11, and ncol[s] holds the particle's cell
 // column.  Also records the positions of the build for the next drift check.
-template <bool CELL>
-__global__ __launch_bounds__(256) void k_nlist_build(const double2* __restrict__ pos, const int* __restrict__ cs,
+// With STAGE (blocks of one tile, for the one-step kernel) the lists are words of
+// kPassOne entries (word j of the S columns at j S), an entry is the byte offset
+// of the neighbour's staged position, or its relative slot in a tile that does
+// not fit, and the last word is filled up with the staged particle far away.
+// Lists, counts and lane_slot of a staged tile are dealt to the lanes of the
+// force pass: first the particles that may have a neighbour across the periodic
+// edge, then the others, each by list length, longest first.  A wave runs as many
+// passes as its longest list, and takes minimum images if one of its lanes has to.
+enum : int { LIST_SLOT = 0, LIST_CELL = 1, LIST_STAGE = 2 };
+template <int MODE>
+__global__ __launch_bounds__(512) void k_nlist_build(const double2* __restrict__ pos, const int* __restrict__ cs,
                                                      const RepDev* __restrict__ reps, const int* __restrict__ tile_rep,
                                                      int BSt, int S, int maxnb, short* __restrict__ nbl,
                                                      unsigned char* __restrict__ nbc, unsigned short* __restrict__ ncol,
-                                                     double2* __restrict__ pref, int* err) {
+                                                     double2* __restrict__ pref, const int* __restrict__ trange,
+                                                     unsigned short* __restrict__ lane_slot, int* err) {
+    constexpr bool CELL = MODE == LIST_CELL, STAGE = MODE == LIST_STAGE;
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     const RepDev& R = reps[tile_rep[min(s, S - 1) / BSt]];
     const bool act = s < S && s - R.slot0 < R.n;
@@ -752,17 +850,23 @@ __global__ __launch_bounds__(256) void k_nlist_build(const double2* __restrict__
     // bit for bit
     const bool inner = nc >= 4 && cx >= 1 && cx < nc - 1 && cy >= 1 && cy < nc - 1;
     const bool interior = __ballot(act && !inner) == 0ull;
-    if (s >= S) return;
-    if (!act) {
-        nbc[s] = 0;
-        return;
+    if (!STAGE) {
+        if (s >= S) return;
+        if (!act) {
+            nbc[s] = 0;
+            return;
+        }
     }
-    pref[s] = p;
+    const TileRanges* __restrict__ T = reinterpret_cast<const TileRanges*>(trange) + blockIdx.x;  // STAGE: one tile per block
+    const bool staged = STAGE && trange && T->base[5] <= kStageMul * (int)blockDim.x;
+    if (act) pref[s] = p;
     const double invL = 1.0 / R.L;
     const double rl2 = R.w * R.w;
     if (CELL) ncol[s] = (unsigned short)cx;
     int cnt = 0;
-    for (int oy = -1; oy <= 1; ++oy) {
+    unsigned long long word = 0;
+    unsigned long long* words = reinterpret_cast<unsigned long long*>(nbl);  // STAGE
+    for (int oy = -1; oy <= 1 && act; ++oy) {
         int rw = cy + oy;
         rw = rw < 0 ? rw + nc : (rw >= nc ? rw - nc : rw);
         const int base = R.cell0 + rw * nc;
@@ -777,6 +881,20 @@ __global__ __launch_bounds__(256) void k_nlist_build(const double2* __restrict__
         const int m1 = CELL && xr - xl >= 2 ? cs[base + xl + 1] : a1;
         const int m2 = CELL && xr - xl >= 3 ? cs[base + xl + 2] : a1;
         const int na = a1 - a0, tot = na + (b1 - b0);
+        // STAGE: staged index of the first particle of either range
+        int sa = 0, sb = 0;
+        if (staged) {
+            auto find = [&](int v) {
+                const int c2 = nc * nc;
+                if (T->whole) v = v < 0 ? v + c2 : (v >= c2 ? v - c2 : v);
+                for (int r = 0; r < 5; ++r)
+                    if (v >= T->lo[r] && v <= T->hi[r]) return T->base[r] + slots_before(cs, R, v) - T->start[r];
+                atomicOr(err, ERR_NLIST);  // not reached: see TileRanges
+                return 0;
+            };
+            sa = find((cy + oy) * nc + xl);
+            if (wrap) sb = find((cy + oy) * nc + (cx == 0 ? nc - 1 : 0));
+        }
         for (int t = 0; t < tot; ++t) {
             const int k = t < na ? a0 + t : b0 + (t - na);
             if (k == s) continue;
@@ -801,13 +919,25 @@ __global__ __launch_bounds__(256) void k_nlist_build(const double2* __restrict__
                     const int idx = k - first;
                     if (idx > 4095) atomicOr(err, ERR_NLIST);
                     e = (((oy + 1) * 3 + (ox + 1)) << 12) | (idx & 4095);
+                } else if (staged) {
+                    e = (int)sizeof(double2) * (t < na ? sa + t : sb + (t - na));
                 } else {
                     e = k - s;
                     if (2 * e >= R.n) e -= R.n;
                     else if (2 * e < -R.n) e += R.n;
                     if (e < -32768 || e > 32767) atomicOr(err, ERR_NLIST);
                 }
-                if (cnt < maxnb) nbl[(long long)cnt * S + s] = (short)e;
+                if constexpr (STAGE) {
+                    if (cnt < maxnb) {
+                        word |= (unsigned long long)(unsigned short)e << (16 * (cnt % kPassOne));
+                        if (cnt % kPassOne == kPassOne - 1) {
+                            words[(long long)(cnt / kPassOne) * S + s] = word;
+                            word = 0;
+                        }
+                    }
+                } else if (cnt < maxnb) {
+                    nbl[(long long)cnt * S + s] = (short)e;
+                }
                 ++cnt;
             }
         }
@@ -816,7 +946,58 @@ __global__ __launch_bounds__(256) void k_nlist_build(const double2* __restrict__
         atomicOr(err, ERR_NLIST);
         cnt = maxnb;
     }
-    nbc[s] = (unsigned char)cnt;
+    if constexpr (!STAGE) {
+        nbc[s] = (unsigned char)cnt;
+    } else {
+        if (cnt % kPassOne) {
+            for (int u = cnt % kPassOne; u < kPassOne && staged; ++u)
+                word |= (unsigned long long)(kStageMul * blockDim.x * sizeof(double2)) << (16 * u);
+            words[(long long)(cnt / kPassOne) * S + s] = word;
+        }
+        if (!staged) {
+            nbc[s] = (unsigned char)cnt;
+            return;  // the whole block
+        }
+        constexpr int kGroups = 64;  // first half: near the edge; by passes, 31 and more together
+        __shared__ int fill[kGroups], longest;
+        __shared__ unsigned short order[512];
+        const int tid = threadIdx.x, tile0 = s - tid;
+        if (tid < kGroups) fill[tid] = 0;
+        if (tid == 0) longest = 0;
+        __syncthreads();
+        // three cells from the edge now: two widths from it until the next build
+        const bool edge = cx < 3 || cx >= nc - 3 || cy < 3 || cy >= nc - 3;
+        const int passes = (cnt + kPassOne - 1) / kPassOne;
+        const int g = (act && edge ? 0 : kGroups / 2) + kGroups / 2 - 1 - min(passes, kGroups / 2 - 1);
+        const int rank = atomicAdd(&fill[g], 1);
+        atomicMax(&longest, passes);
+        __syncthreads();
+        int v = 0, x = 0;
+        if (tid < kGroups) {
+            x = v = fill[tid];
+            for (int o = 1; o < kGroups; o <<= 1) {
+                const int y = __shfl_up(x, o, 64);
+                if (tid >= o) x += y;
+            }
+            fill[tid] = x - v;
+        }
+        __syncthreads();
+        const int lane = fill[g] + rank;
+        order[lane] = (unsigned short)tid;
+        nbc[tile0 + lane] = (unsigned char)cnt;
+        __syncthreads();  // and the words of this block are written
+        const int q = order[tid], rows = longest;
+        lane_slot[s] = (unsigned short)q;
+        for (int j0 = 0; j0 < rows; j0 += 4) {
+            unsigned long long w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = words[(long long)min(j0 + u, rows - 1) * S + tile0 + q];
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (j0 + u < rows) words[(long long)(j0 + u) * S + s] = w[u];
+        }
+    }
 }
 
 // Pair force on a particle at p from the nn entries of its neighbour list
@@ -831,10 +1012,6 @@ __global__ __launch_bounds__(256) void k_nlist_build(const double2* __restrict__
 // a multiple of U, so rows j0 .. j0 + U - 1 exist whenever j0 < nn: they are
 // loaded without waiting for the count nn, and entries past nn are replaced
 // by 0 (a valid index) before they are used as one.
-constexpr int kListU = 2;              // fused kernels (lists ordered by length within a tile)
-constexpr int kListUOne = 4;           // one-step kernel (slot order: fewer, longer passes keep more loads in flight)
-constexpr int kListPre = 4 * kListU;  // rows loaded ahead for a thread's first particle (maxnb >= 16)
-constexpr int kListPreEvent = 2 * kListU;  // the same in the event and binning launches
 static_assert(kListPre % kListU == 0, "whole passes of the fused kernels' rows loaded ahead");
 
 template <int N, typename Entry>
@@ -980,16 +1157,6 @@ __device__ __forceinline__ void nlist_force(double2 p, int nn, const Entry* __re
     fy = F32 ? (double)by : ay;
 }
 
-template <bool F32, int U, typename Entry, typename Fetch>
-__device__ __forceinline__ void nlist_force(double2 p, int nn, const Entry* __restrict__ list, unsigned int off,
-                                            unsigned int stride, Fetch fetch, bool interior, double L, double invL,
-                                            double rc2, double eps24, float rc2f, float eps24f, double& fx,
-                                            double& fy) {
-    const int none[1] = {};
-    nlist_force<F32, U, 1>(p, nn, list, off, stride, fetch, interior, L, invL, rc2, eps24, rc2f, eps24f, fx, fy,
-                           none, false);
-}
-
 // Velocity-Verlet update with the force at the current position: complete
 // the half-step velocity (not on the first step, whose velocity is a full-step
 // one), kick, drift, wrap into [0, L) with the image change in (wx, wy).  The
@@ -1016,13 +1183,28 @@ __device__ __forceinline__ double2 vv_update(double2 p, double2& v, double fx, d
     return pn;
 }
 
-// One velocity-Verlet step, one thread per slot, pair forces over the slot's
-// neighbour list (FIRST: the stored velocity is a full-step one; CG: this step
-// ends a coarse step).  Per neighbour: one coalesced index load, one position
-// gather, the minimum image through rint, and the pair force with the
-// reciprocal from the hardware estimate refined by Newton steps.
-template <int BS, bool F32, bool FIRST, bool CG>
+// One velocity-Verlet step, one tile of slots per block, pair forces over
+// neighbour lists (FIRST: the stored velocity is a full-step one; CG: this step
+// ends a coarse step).  The block stages its own and its neighbours' positions
+// in LDS (see TileRanges) with coalesced loads; the lanes of the force pass take
+// the tile's particles in the order of the list build and hand the forces back
+// through LDS, so that every global access of the update stays coalesced.  A
+// tile that stages more than kStageMul BS particles gathers from global
+// memory, in slot order, as every tile does without STAGE.
+// Vector issue (24 instructions per list entry of each wave's longest list, 15
+// of them FP64) and traffic (about 100 B per particle-step: state 64, list 32)
+// share the bound, behind a launch and first loads of 4-5 us.  816,000 particles
+// at phi = 0.4: 25.5 us per step with neighbours gathered in slot order, entry by
+// entry; 21.4 here.  Where lists are short their padding costs more than the
+// gathers: at phi = 0.08, 0.16 and 0.2 (2.9, 5.8 and 7.2 listed neighbours) 2^20
+// particles took 17.8, 21.5 and 23.2 us gathered and 20.0, 21.7 and 22.5 staged,
+// 2^16 particles 4.28, 5.11 and 5.36 gathered and 4.78, 5.14 and 5.32 staged, so
+// the line lies at kStageMean = 7.  Blocks of 256: 128 took 24.9 and 64 27.3
+// against 23.5 us per step, rebuilds included.
+template <int BS, bool F32, bool FIRST, bool CG, bool STAGE>
 __global__ __launch_bounds__(BS) void k_step_nlist(StepArgs a) {
+    __shared__ double2 xs[STAGE ? kStageMul * BS + 1 : 1];
+    __shared__ double2 force[STAGE ? BS : 1];
     __shared__ int hist[MDLG_NCOUNTS];
     __shared__ double red[BS / 64][4];
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -1036,24 +1218,112 @@ __global__ __launch_bounds__(BS) void k_step_nlist(StepArgs a) {
     const bool act = tid < nact_blk;
     if (CG && tid < MDLG_NCOUNTS) hist[tid] = 0;
 
-    const double2 p = a.pin[s];
-    double2 v = a.vel[s];
-    const int nn = act ? a.nbc[s] : 0;
-    // A wave whose particles all lie two cell widths or more inside the box has
-    // no neighbour across the periodic edge: its separations need no image.
-    const double edge = 2.0 * R.w;
-    const bool near_edge = act && (p.x < edge || p.x > L - edge || p.y < edge || p.y > L - edge);
-    const bool interior = __ballot(near_edge) == 0ull;
-    const int srel = s - R.slot0, nr = R.n, slot0 = R.slot0;
+    const int nr = R.n, slot0 = R.slot0;
     const double2* __restrict__ pin = a.pin;
-    auto fetch = [&](int k) {
-        int kr = srel + k;
-        kr = kr < 0 ? kr + nr : (kr >= nr ? kr - nr : kr);
-        return pin[slot0 + kr];
-    };
+    const TileRanges* __restrict__ T = reinterpret_cast<const TileRanges*>(a.trange) + tile;
+    const int total = STAGE ? T->base[5] : 0;
+    const bool staged = STAGE && total <= kStageMul * BS;
+    const unsigned long long* __restrict__ words = reinterpret_cast<const unsigned long long*>(a.nbl) + s;
+    constexpr int PRE = STAGE ? kPreOne : kPreShort;
+    unsigned long long pre[PRE];
+#pragma unroll
+    for (int b = 0; b < PRE; ++b) pre[b] = words[(unsigned int)b * (unsigned int)a.nslots];
+    const int nn = a.nbc[s];  // 0 for pad slots
+    const int q = STAGE ? a.lane_slot[s] : 0;  // of a staged tile
+    double2 v = a.vel[s];
+    double2 p;
     double fx, fy;
-    nlist_force<F32, kListUOne>(p, nn, a.nbl, (unsigned int)s, (unsigned int)a.nslots, fetch, interior, L, invL, R.rc2, R.eps24,
-                     R.rc2f, R.eps24f, fx, fy);
+    if (staged) {
+        const int b1 = T->base[1], b2 = T->base[2], b3 = T->base[3], b4 = T->base[4];
+        const int o0 = T->start[0], o1 = T->start[1] - b1, o2 = T->start[2] - b2, o3 = T->start[3] - b3, o4 = T->start[4] - b4;
+        const int own = T->own;
+        // at most 2^30 / 16 slots: 32-bit byte offsets
+        auto at = [&](int k) {
+            return *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(pin + slot0) + ((unsigned int)k << 4));
+        };
+        double zx[kStageMul], zy[kStageMul];
+#pragma unroll
+        for (int u = 0; u < kStageMul; ++u) {
+            const int i = tid + u * BS;
+            int k = i + (i < b1 ? o0 : (i < b2 ? o1 : (i < b3 ? o2 : (i < b4 ? o3 : o4))));
+            k = k < 0 ? k + nr : (k >= nr ? k - nr : k);
+            const double2 z = at(i < total ? k : 0);
+            zx[u] = z.x;
+            zy[u] = z.y;
+        }
+#pragma unroll
+        for (int u = 0; u < kStageMul; ++u) xs[tid + u * BS] = make_double2(zx[u], zy[u]);
+        if (tid == 0) xs[kStageMul * BS] = make_double2(4.0 * L, 4.0 * L);  // the one far away
+        __syncthreads();
+        p = xs[act ? own + tid : 0];
+        const double2 pq = xs[q < nact_blk ? own + q : 0];
+        // A wave whose particles all lie two cell widths or more inside the box has
+        // no neighbour across the periodic edge: its separations need no image.
+        const double edge = 2.0 * R.w;
+        const bool near_edge = q < nact_blk && (pq.x < edge || pq.x > L - edge || pq.y < edge || pq.y > L - edge);
+        const bool interior = __ballot(near_edge) == 0ull;
+        double ax = 0.0, ay = 0.0;
+        float bx = 0.0f, by = 0.0f;
+        auto pass = [&](unsigned long long w, int j0) {
+            double2 z[kPassOne];
+#pragma unroll
+            for (int u = 0; u < kPassOne; ++u)
+                z[u] = *reinterpret_cast<const double2*>(reinterpret_cast<const char*>(xs) + ((w >> (16 * u)) & 0xffffu));
+#pragma unroll
+            for (int u = 0; u < kPassOne; ++u) {
+                double dx = pq.x - z[u].x, dy = pq.y - z[u].y;
+                if (!interior && j0 + u < nn) {  // no image of the one far away
+                    dx = min_image_rint(dx, L, invL);
+                    dy = min_image_rint(dy, L, invL);
+                }
+                // the one far away lies beyond the cutoff
+                pair_add<F32>(dx, dy, true, R.rc2, R.eps24, R.rc2f, R.eps24f, ax, ay, bx, by);
+            }
+        };
+#pragma unroll
+        for (int b = 0; b < PRE; ++b)
+            if (b * kPassOne < nn) pass(pre[b], b * kPassOne);
+        for (int j0 = PRE * kPassOne; j0 < nn; j0 += kPassOne)
+            pass(words[(unsigned int)(j0 / kPassOne) * (unsigned int)a.nslots], j0);
+        force[q] = F32 ? make_double2((double)bx, (double)by) : make_double2(ax, ay);
+        __syncthreads();
+        fx = force[tid].x;
+        fy = force[tid].y;
+    } else {
+        p = pin[s];
+        const double edge = 2.0 * R.w;
+        const bool near_edge = act && (p.x < edge || p.x > L - edge || p.y < edge || p.y > L - edge);
+        const bool interior = __ballot(near_edge) == 0ull;
+        const int srel = s - slot0;
+        double ax = 0.0, ay = 0.0;
+        float bx = 0.0f, by = 0.0f;
+        auto pass = [&](unsigned long long w, int j0) {
+            double2 z[kPassOne];
+#pragma unroll
+            for (int u = 0; u < kPassOne; ++u) {
+                int kr = srel + (int)(short)(w >> (16 * u));  // srel, the particle itself, past the list's end
+                kr = kr < 0 ? kr + nr : (kr >= nr ? kr - nr : kr);
+                z[u] = pin[slot0 + kr];
+            }
+#pragma unroll
+            for (int u = 0; u < kPassOne; ++u) {
+                double dx = p.x - z[u].x, dy = p.y - z[u].y;
+                if (!interior) {
+                    dx = min_image_rint(dx, L, invL);
+                    dy = min_image_rint(dy, L, invL);
+                }
+                // a zero separation gives a NaN, which the select discards
+                pair_add<F32>(dx, dy, j0 + u < nn, R.rc2, R.eps24, R.rc2f, R.eps24f, ax, ay, bx, by);
+            }
+        };
+#pragma unroll
+        for (int b = 0; b < PRE; ++b)
+            if (b * kPassOne < nn) pass(pre[b], b * kPassOne);
+        for (int j0 = PRE * kPassOne; j0 < nn; j0 += kPassOne)
+            pass(words[(unsigned int)(j0 / kPassOne) * (unsigned int)a.nslots], j0);
+        fx = F32 ? (double)bx : ax;
+        fy = F32 ? (double)by : ay;
+    }
     int idx = MDLG_NQ;
     double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;
     if (act) {
@@ -2559,6 +2829,8 @@ struct lj_md {
     short* nbl = nullptr;     // neighbour lists (step kernel 3)
     unsigned char* nbc = nullptr;
     unsigned short* ncol = nullptr;  // cell column of each slot (tile list builder)
+    int* trange = nullptr;              // [ntile][kRangeInts] (one-step kernel over lists)
+    unsigned short* lane_slot = nullptr;  // [S]
     // two ordinary steps per launch (step kernel 3)
     bool two_step = false;
     bool three_step = false;          // also three ordinary steps per launch (implies two_step)
@@ -2644,7 +2916,8 @@ void launch_step_bs(const lj_md* md, hipStream_t st, const StepArgs& a, hipEvent
     if (md->variant == 2) {
         EXT_LAUNCH((k_step_tile<BS, F32, FIRST, CG>), BS, md->TT);
     } else if (md->variant == 3) {
-        EXT_LAUNCH((k_step_nlist<BS, F32, FIRST, CG>), BS, md->ntile);
+        if (md->trange) EXT_LAUNCH((k_step_nlist<BS, F32, FIRST, CG, true>), BS, md->ntile);
+        else EXT_LAUNCH((k_step_nlist<BS, F32, FIRST, CG, false>), BS, md->ntile);
     } else if (md->ubatch <= 4) {
         EXT_LAUNCH((k_step_gather<BS, F32, FIRST, CG, 4>), BS, md->ntile);
     } else if (md->ubatch <= 8) {
@@ -2679,6 +2952,8 @@ StepArgs make_args(lj_md* md) {
     a.stage_max = md->stage_max;
     a.nbl = md->nbl;
     a.nbc = md->nbc;
+    a.trange = md->trange;
+    a.lane_slot = md->lane_slot;
     a.plist = md->plist;
     a.pcnt = md->pcnt;
     a.tlist = md->tlist;
@@ -2879,17 +3154,25 @@ hipError_t launch_rebuild(lj_md* md, hipStream_t st) {
     b.snap_o = md->snap[o];
     b.snap_n = md->snap[o ^ 1];
     hipLaunchKernelGGL(k_place, dim3((S + 255) / 256), dim3(256), 0, st, (const int*)md->cs, (const int*)md->key,
-                       (const int*)md->perm, (const int*)md->permid, S, b, md->variant == 3 ? nullptr : md->cellof);
-    // the tile lists take entries by cell and index within the cell; the
-    // one-step kernel takes slot offsets
-    if (md->variant == 3 && md->two_step)
-        hipLaunchKernelGGL(k_nlist_build<true>, dim3((S + 255) / 256), dim3(256), 0, st, (const double2*)b.pos_n,
-                           (const int*)md->cs, (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, md->BS, S,
-                           md->maxnb, md->nbl, md->nbc, md->ncol, md->pref, md->d_err);
-    else if (md->variant == 3)
-        hipLaunchKernelGGL(k_nlist_build<false>, dim3((S + 255) / 256), dim3(256), 0, st, (const double2*)b.pos_n,
-                           (const int*)md->cs, (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, md->BS, S,
-                           md->maxnb, md->nbl, md->nbc, (unsigned short*)nullptr, md->pref, md->d_err);
+                       (const int*)md->perm, (const int*)md->permid, S, b,
+                       md->variant != 3 || md->trange ? md->cellof : nullptr);
+    // the tile lists take entries by cell and index within the cell, the
+    // one-step kernel staged indices, the block-per-replica kernel slot offsets
+    auto lists = [&](auto kernel, int grid, int bs) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(bs), 0, st, (const double2*)b.pos_n, (const int*)md->cs,
+                           (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, md->BS, S, md->maxnb, md->nbl, md->nbc,
+                           md->ncol, md->pref, (const int*)md->trange, md->lane_slot, md->d_err);
+    };
+    if (md->variant == 3 && md->two_step) {
+        lists(k_nlist_build<LIST_CELL>, (S + 255) / 256, 256);
+    } else if (md->variant == 3 && md->resident) {
+        lists(k_nlist_build<LIST_SLOT>, (S + 255) / 256, 256);
+    } else if (md->variant == 3) {
+        if (md->trange) hipLaunchKernelGGL(k_tile_ranges, dim3((md->ntile + 63) / 64), dim3(64), 0, st, (const int*)md->cs,
+                           (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, (const int*)md->cellof, md->BS, md->ntile,
+                           md->trange);
+        lists(k_nlist_build<LIST_STAGE>, md->ntile, md->BS);
+    }
     if (md->two_step)
         hipLaunchKernelGGL(k_pair_build<kPairBuildBS>, dim3(md->npt), dim3(kPairBuildBS), 0, st, (const int*)md->cs,
                            (const RepDev*)md->d_reps, (const int*)md->d_ptrep, (const short*)md->nbl,
@@ -3377,7 +3660,7 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
          A(dalloc(&md->d_mpart, part_tiles * MDLG_NMOMENTS)) && A(dalloc(&md->d_event_k, 1)) &&
          A(hipStreamCreateWithFlags(&md->cap, hipStreamNonBlocking));
     if (ok && md->variant == 3) {
-        static_assert(248 % kListU == 0 && 248 % kListUOne == 0 && kListPre <= 16, "list rows are read in whole passes");
+        static_assert(248 % kListU == 0 && 248 % kPassOne == 0 && kListPre <= 16, "list rows are read in whole passes");
         for (int r = 0; r < n_rep; ++r) {
             // list entries are 16-bit slot offsets: a neighbour lies within about
             // three cell rows of a particle in cell order
@@ -3391,6 +3674,8 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
             return destroy_on_fail(md, fail(MDLG_EINVAL, "lj_md_init: neighbour lists of this size exceed 2^30 "
                                                          "entries; use step_kernel 1"));
         ok = A(dalloc(&md->nbl, (size_t)md->maxnb * md->S)) && A(dalloc(&md->nbc, md->S)) && A(dalloc(&md->pref, md->S));
+        if (ok && !md->two_step && !md->resident && mean_max >= kStageMean)
+            ok = A(dalloc(&md->trange, (size_t)md->ntile * kRangeInts)) && A(dalloc(&md->lane_slot, md->S));
         if (ok && md->two_step)
             ok = A(dalloc(&md->d_ptrep, md->npt)) && A(dalloc(&md->plist, (size_t)md->npt * kPairCap)) &&
                  A(dalloc(&md->pcnt, md->npt)) && A(dalloc(&md->tlist, (size_t)md->npt * md->maxnb * kPairCap)) &&
@@ -3971,7 +4256,7 @@ extern "C" void lj_md_destroy(lj_md* md) {
     if (!md) return;
     clear_graphs(md);
     if (md->cap) (void)hipStreamDestroy(md->cap);
-    void* ptrs[] = {md->d_reps, md->d_tile_rep, md->d_ttile_rep, md->d_tinfo, md->nbl, md->nbc, md->ncol, md->pref, md->d_hpart, md->pos[0], md->pos[1], md->vel[0], md->vel[1], md->img[0],
+    void* ptrs[] = {md->d_reps, md->d_tile_rep, md->d_ttile_rep, md->d_tinfo, md->nbl, md->nbc, md->ncol, md->trange, md->lane_slot, md->pref, md->d_hpart, md->pos[0], md->pos[1], md->vel[0], md->vel[1], md->img[0],
                     md->img[1], md->id[0], md->id[1], md->snap[0], md->snap[1], md->key, md->rank, md->perm, md->permid,
                     md->cellof, md->cnt, md->cs, md->bsum, md->d_err, md->d_epart, md->d_eout, md->d_vmax,
                     md->d_mpart, md->d_event_k, md->d_ptrep, md->plist, md->pcnt, md->tlist, md->tcnt};

@@ -688,6 +688,41 @@ def test_block_per_replica_equals_one_step(sizes, phi, kT, kw):
     torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("sizes,phi,kT,kw", [
+    ([42], 0.4, 20.0, {"block_size": 64}), ([513], 0.3, 5.0, {"block_size": 512}), ([1024], 0.4, 5.0, {"block_size": 128}),
+    ([2047], 0.25, 20.0, {"rebuild_every": 6}), ([1100, 64, 1999], 0.3, 5.0, {"block_size": 64}),
+    ([1025, 300], 0.4, 5.0, {"force_bits": 32, "block_size": 128}), ([1025, 300], 0.1, 5.0, {"block_size": 64}),
+    ([1989], "bands", 0.1, {"block_size": 64}), ([1989], "bands", 0.1, {"block_size": 128}), ([1989], "bands", 0.1, {}),
+])
+def test_one_step_staged_tiles_equal_block_per_replica(sizes, phi, kT, kw):
+    """The one-step list kernel at every block size against one block per replica, bit for bit: tiles of one and of
+    several rows of cells, across the periodic edges, the whole box as one tile, a last tile of few particles, tiles
+    whose neighbours are too many to stage (a dense band beside a dilute one), short
+    lists (not staged)."""
+    import paper_2101_01160_amd as m
+    print(f"one step staged {sizes} phi={phi} {kw}", flush=True)
+    if phi == "bands":
+        L = 64.0
+        g, y, x2, y2 = 0.3 + 1.05 * np.arange(60), 0.3 + 1.05 * np.arange(30), 1 + 3.0 * np.arange(21), 34 + 3.0 * np.arange(9)
+        pts = np.concatenate([np.stack(np.meshgrid(a, b), axis=-1).reshape(-1, 2) for a, b in ((g, y), (x2, y2))])
+        states = [(pts, mi.maxwell_velocities(sizes[0], kT, np.random.default_rng(2)), L)]
+    else:
+        states = [mi.initial_state(n, phi, kT, 170 + k) for k, n in enumerate(sizes)]
+    pos, vel = (np.concatenate([s[k] for s in states]) for k in (0, 1))
+    out = []
+    for fuse in (0, 1):
+        b = m.LJSystem(_cuda(pos), _cuda(vel), params=[m.lj_params(n, s[2], fuse_steps=fuse, **kw)
+                                                       for n, s in zip(sizes, states)])
+        acc = b.attach_cg([max(7, int(s[2] / 2.0)) for s in states], 5, u=(0.1, -0.3))
+        for c in [1] * 30:  # the same rebuild steps
+            b.step(c)
+        b.check()
+        out.append([_np(t) for t in b.state()] + [_np(acc.counts)])
+        b.close()
+    for x, y in zip(*out):
+        assert np.array_equal(x, y)
+
+
 def test_block_per_replica_reports_drift_and_times_steps():
     pos0, vel0, L = mi.initial_state(900, 0.0784, 20.0, 4)
     sysm = gpu_system(pos0, vel0, L)
