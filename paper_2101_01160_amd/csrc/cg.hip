@@ -59,7 +59,8 @@ __device__ __forceinline__ int lattice_move(double t0, int i0, double t1, int i1
 
 constexpr int kCgU = 4;            // particles of a thread in flight
 constexpr int kCgMaxBlocks = 1024; // four per compute unit
-constexpr size_t kCgScratch = (size_t)kCgMaxBlocks * (4 * sizeof(double) + MDLG_NCOUNTS * sizeof(int));
+constexpr size_t kCgBlockBytes = 4 * sizeof(double) + MDLG_NCOUNTS * sizeof(int);  // partials of a block
+constexpr size_t kCgScratch = kCgMaxBlocks * kCgBlockBytes;
 
 // Box-frame displacement over the coarse step, rounded as written.
 __device__ __forceinline__ double unwrapped_delta(double xc, double xp, int di, double L) {
@@ -237,6 +238,8 @@ mdlg_status check_cg_args(const char* who, const mdlg_lattice* lat, double box_l
     return MDLG_OK;
 }
 
+int cg_blocks(long long n) { return (int)std::min<long long>((n + kCgBS - 1) / kCgBS, kCgMaxBlocks); }
+
 // The event itself, with its partials in `part` (kCgScratch bytes).  Where calls
 // may overlap on the same `part`, `shared` keeps the counts out of it.
 hipError_t coarse_grain_launch(const mdlg_lattice* lat, double box_l, int64_t n, const double* pos_prev,
@@ -251,7 +254,7 @@ hipError_t coarse_grain_launch(const mdlg_lattice* lat, double box_l, int64_t n,
         if (e != hipSuccess) return e;
     }
     if (n == 0) return hipSuccess;
-    const int nb = (int)std::min<long long>((n + kCgBS - 1) / kCgBS, kCgMaxBlocks);
+    const int nb = cg_blocks(n);
     CgArgs a{};
     a.xp = (const double2*)pos_prev;
     a.ip = (const int2*)img_prev;
@@ -270,7 +273,7 @@ hipError_t coarse_grain_launch(const mdlg_lattice* lat, double box_l, int64_t n,
     a.cell_acc = cell_acc;
     a.nb = nb;
     a.mpart = (double*)part;
-    a.hpart = (int*)(a.mpart + 4 * (size_t)kCgMaxBlocks);
+    a.hpart = (int*)(a.mpart + 4 * (size_t)nb);
     a.counts = shared ? (unsigned long long*)counts : nullptr;
     hipLaunchKernelGGL(k_coarse_grain<kCgBS>, dim3((unsigned)nb), dim3(kCgBS), 0, st, a);
     hipError_t e = hipGetLastError();
@@ -293,7 +296,7 @@ extern "C" mdlg_status mdlg_coarse_grain(const mdlg_lattice* lat, double box_l, 
     if (s != MDLG_OK) return s;
     hipStream_t st = (hipStream_t)stream;
     void* part = nullptr;
-    if (n > 0) MDLG_HIP(hipMallocAsync(&part, kCgScratch, st));
+    if (n > 0) MDLG_HIP(hipMallocAsync(&part, kCgBlockBytes * cg_blocks(n), st));
     hipError_t e = coarse_grain_launch(lat, box_l, n, pos_prev, img_prev, k_prev, pos_cur, img_cur, k_cur, counts,
                                        moments, n_event, cell_acc, part, false, st);
     hipError_t e2 = part ? hipFreeAsync(part, st) : hipSuccess;
