@@ -25,18 +25,38 @@ constexpr int kVacfSlots = 8;            // lags of one lane
 constexpr int kVacfLds = 160 * 1024;     // LDS of a compute unit
 constexpr int kVacfBlocks = 2048;        // blocks aimed at: each adds several groups before it writes partials
 
+// Which particles block b takes: replica r has blocks b0[r] .. b0[r + 1] - 1 of
+// `span` particles.  (A table of all blocks, copied from pageable memory on each
+// call, took up to 30 us for 3000 blocks.)
+struct VacfMap {
+    const long long* offsets;  // [n_rep + 1]
+    const int* b0;             // [n_rep + 1]
+    int n_rep;
+    int span;
+};
 struct VacfBlock {
     long long start;
     int count;
-    int rep;
 };
 
+__device__ __forceinline__ VacfBlock vacf_block(const VacfMap& m, int b) {
+    int r = 0, hi = m.n_rep;  // b0[r] <= b < b0[hi]
+    while (hi - r > 1) {
+        const int mid = (r + hi) / 2;
+        if (m.b0[mid] <= b) r = mid;
+        else hi = mid;
+    }
+    const long long start = m.offsets[r] + (long long)(b - m.b0[r]) * m.span;
+    const long long left = m.offsets[r + 1] - start;
+    return {start, (int)(left < m.span ? left : m.span)};
+}
+
 __global__ __launch_bounds__(kVacfBS) void k_vacf(const double2* __restrict__ vel, long long n_tot, int n_snap,
-                                                  const VacfBlock* __restrict__ blocks, const int* __restrict__ lags,
+                                                  VacfMap map, const int* __restrict__ lags,
                                                   int n_block, double* __restrict__ part) {
     __shared__ double ws[kVacfBS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const VacfBlock blk = blocks[blockIdx.x];
+    const VacfBlock blk = vacf_block(map, blockIdx.x);
     const int s = blockIdx.y;
     const int l = lags[s];
     double acc = 0.0;
@@ -75,7 +95,7 @@ __global__ __launch_bounds__(kVacfBS) void k_vacf(const double2* __restrict__ ve
 // is then skipped by the whole wave.  The waves take the origins in turn.
 template <int PT>
 __global__ __launch_bounds__(kVacfLdsBS) __attribute__((amdgpu_waves_per_eu(4))) void k_vacf_lds(const double2* __restrict__ vel, long long n_tot, int n_snap,
-                                                         const VacfBlock* __restrict__ blocks,
+                                                         VacfMap map,
                                                          const int* __restrict__ lags, int n_lag, int n_block,
                                                          double* __restrict__ part) {
     static_assert(kVacfSlots == 8, "the runs below");
@@ -84,7 +104,7 @@ __global__ __launch_bounds__(kVacfLdsBS) __attribute__((amdgpu_waves_per_eu(4)))
     __shared__ double red[W][NL];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int i = lane % PT, g = lane / PT;
-    const VacfBlock blk = blocks[blockIdx.x];
+    const VacfBlock blk = vacf_block(map, blockIdx.x);
     for (int b0 = 0; b0 < n_lag; b0 += NL) {
         int l[kVacfSlots], lo[kVacfSlots];  // the lane's lag, the smallest lag of the slot
         double acc[kVacfSlots];
@@ -185,35 +205,41 @@ extern "C" mdlg_status mdlg_vacf(int32_t n_rep, const int64_t* offsets, int32_t 
     int pt = 8;
     while (pt > 1 && 2 * (lds_of(pt) + red_of(pt)) > kVacfLds) pt /= 2;
     const size_t lds = lds_of(pt);
-    const bool staged = lds + red_of(pt) <= kVacfLds;
+    // k_vacf for few products of each velocity: 25,000 particles, 30 snapshots, 7
+    // lags took 54 us there and 74 staged, 99,856 with 20 and 5 70 and 90, 25,000
+    // with 60 and 12 72 and 79; with more of either 99,856, 30 and 7 took 105 and
+    // 95, 99,856, 60 and 12 252 and 111.  Its threads each sum one lag over all
+    // snapshots, which 300 of them make too long a chain (2000 particles, 3 lags:
+    // 82 us against 53; 120: 61 and 51).
+    const bool few = n_snap <= 64 && (n_lag <= 5 || n_tot * n_lag <= 300000);
+    const bool staged = !few && lds + red_of(pt) <= kVacfLds;
     // particles of a block: whole groups, as many as leave about kVacfBlocks blocks
     const long long span = staged ? std::max<long long>(1, n_tot / pt / kVacfBlocks) * pt : kVacfBS;
-    std::vector<VacfBlock> blocks;
+    if (span > (1 << 30)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
     std::vector<int> rep_block0(n_rep + 1, 0);
+    long long n_block = 0;
     for (int r = 0; r < n_rep; ++r) {
         const long long n = offsets[r + 1] - offsets[r];
         if (n < 0) return fail(MDLG_EINVAL, std::string(who) + "offsets must be non-decreasing");
-        rep_block0[r] = (int)blocks.size();
-        for (long long s0 = 0; s0 < n; s0 += span)
-            blocks.push_back({offsets[r] + s0, (int)std::min<long long>(n - s0, span), r});
-        if (blocks.size() >= (1u << 24)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
+        n_block += (n + span - 1) / span;
+        if (n_block >= (1 << 24)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
+        rep_block0[r + 1] = (int)n_block;
     }
-    rep_block0[n_rep] = (int)blocks.size();
-    if (blocks.empty()) return MDLG_OK;
+    if (n_block == 0) return MDLG_OK;
     // lags in ascending order, and where each belongs in the output
     std::vector<int> order(n_lag), sorted(n_lag);
     for (int s = 0; s < n_lag; ++s) order[s] = s;
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return lags[a] < lags[b]; });
     for (int s = 0; s < n_lag; ++s) sorted[s] = lags[order[s]];
     hipStream_t st = (hipStream_t)stream;
-    const size_t nb = blocks.size();
-    const size_t off_b0 = (sizeof(VacfBlock) * nb + 255) / 256 * 256;
+    const size_t nb = n_block;
+    const size_t off_b0 = (sizeof(long long) * (n_rep + 1) + 255) / 256 * 256;
     const size_t off_lags = off_b0 + (sizeof(int) * (n_rep + 1) + 255) / 256 * 256;
     const size_t off_order = off_lags + (sizeof(int) * n_lag + 255) / 256 * 256;
     const size_t off_part = off_order + (sizeof(int) * n_lag + 255) / 256 * 256;
     const size_t total = off_part + sizeof(double) * nb * n_lag;
     std::vector<unsigned char> host(off_part, 0);
-    std::memcpy(host.data(), blocks.data(), sizeof(VacfBlock) * nb);
+    std::memcpy(host.data(), offsets, sizeof(long long) * (n_rep + 1));
     std::memcpy(host.data() + off_b0, rep_block0.data(), sizeof(int) * (n_rep + 1));
     std::memcpy(host.data() + off_lags, sorted.data(), sizeof(int) * n_lag);
     std::memcpy(host.data() + off_order, order.data(), sizeof(int) * n_lag);
@@ -221,7 +247,7 @@ extern "C" mdlg_status mdlg_vacf(int32_t n_rep, const int64_t* offsets, int32_t 
     MDLG_HIP(hipMallocAsync((void**)&dev, total, st));
     hipError_t e = hipMemcpyAsync(dev, host.data(), off_part, hipMemcpyHostToDevice, st);
     const bool copied = e == hipSuccess;
-    const VacfBlock* d_blocks = (const VacfBlock*)dev;
+    const VacfMap map{(const long long*)dev, (const int*)(dev + off_b0), n_rep, (int)span};
     const int* d_lags = (const int*)(dev + off_lags);
     double* part = (double*)(dev + off_part);
     if (e == hipSuccess && staged) {
@@ -231,13 +257,13 @@ extern "C" mdlg_status mdlg_vacf(int32_t n_rep, const int64_t* offsets, int32_t 
                 le = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kVacfLds - (int)red_of(pt));
             if (le != hipSuccess) return le;
             hipLaunchKernelGGL(kernel, dim3((unsigned)nb), dim3(kVacfLdsBS), lds, st, (const double2*)vel, n_tot, n_snap,
-                               d_blocks, d_lags, n_lag, (int)nb, part);
+                               map, d_lags, n_lag, (int)nb, part);
             return hipGetLastError();
         };
         e = pt == 8 ? launch(k_vacf_lds<8>) : pt == 4 ? launch(k_vacf_lds<4>) : pt == 2 ? launch(k_vacf_lds<2>) : launch(k_vacf_lds<1>);
     } else if (e == hipSuccess) {
         hipLaunchKernelGGL(k_vacf, dim3((unsigned)nb, (unsigned)n_lag), dim3(kVacfBS), 0, st, (const double2*)vel, n_tot,
-                           n_snap, d_blocks, d_lags, (int)nb, part);
+                           n_snap, map, d_lags, (int)nb, part);
         e = hipGetLastError();
     }
     if (e == hipSuccess) {

@@ -50,6 +50,19 @@ def test_trajectory_lengths(P, n):
     assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("P,n,k", [(64, 4285, 70), (64, 4286, 70), (64, 60001, 5), (64, 50001, 6), (65, 300, 3)])
+def test_edges_of_the_staging_rule(P, n, k):
+    """Few products of each velocity (up to 64 snapshots, and 5 lags or 300,000 pairs of particle and lag) are summed
+    without staging; empty replicas between, before and after; sums of n P products to 1e-12 of C(0)."""
+    rng = np.random.default_rng(P + n)
+    vel = rng.normal(0.0, 4.0, (P, n, 2))
+    lags = [int(l) for l in rng.integers(0, P, k - 1)] + [0]
+    offsets = [0, 0, n // 3, n // 3, n // 3, n - 1, n, n]
+    got = run(offsets, vel, lags)
+    ref = omd.vacf_sums(np.array(offsets), vel, lags)
+    assert np.abs(got - ref).max() <= 1e-12 * np.abs(ref).max()
+
+
 def test_md_velocities_and_lambda():
     import torch
 
