@@ -23,7 +23,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kIn = 6, kHid = 256, kOut = 49, kOutP = 64;
 constexpr long kW1 = 0, kB1 = 1536, kW2 = 1792, kB2 = 67328, kW3 = 67584, kB3 = 133120, kW4 = 133376, kB4 = 145920;
 constexpr long kParams = 145969;
-constexpr int kMaxSplit = 32;
+constexpr int kMaxSplit = 16;
 // Fixed input map of x = (phi, kT, dt_cg/dx, |u|, cos, sin): phi / 0.4,
 // ln kT / ln 20, (ln(dt_cg/dx) + 6) / 1.5, and the drift as the vector
 // 5 |u| (cos, sin) with its length 5 |u|; fp32, every operation rounded once.
@@ -627,10 +627,12 @@ hipError_t gradient_partials(mdlg_mlp* m, const float* x, const float* R, int B,
                        (const bf16*)m->wc, t, m->loss_b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // a block or two per compute unit (40 tiles x 8 splits; 16 splits
-    // made the products and the sums 0.6 and 0.9 us longer for 2048 samples), at least four k steps in each
-    const long want = std::min<long>(t.steps <= 128 ? 8 : kMaxSplit, std::max<long>(1, t.steps / 4));
-    const int chunk = (int)((t.steps + want - 1) / want);
+    // at least eight k steps in each of a power of two of splits, up to 16 (40
+    // tiles x 8 splits are a block or two per compute unit: for 2048 samples 16
+    // splits made the products and the sums 0.6 and 0.9 us longer)
+    int want = 1;
+    while (2 * want <= kMaxSplit && B >= 16 * want * kTK) want *= 2;
+    const int steps = (B + kTK - 1) / kTK, chunk = (steps + want - 1) / want;
     *splits = (int)((t.steps + chunk - 1) / chunk);
     hipLaunchKernelGGL(k_train_wgrad, dim3(kWgTiles, (unsigned)*splits), dim3(256), 0, st, t, chunk, m->part);
     return hipGetLastError();
