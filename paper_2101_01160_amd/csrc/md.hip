@@ -823,7 +823,7 @@ __global__ void k_tile_ranges(const int* __restrict__ cs, const RepDev* __restri
 // With STAGE (blocks of one tile, for the one-step kernel) the lists are words of
 // kPassOne entries (word j of the S columns at j S), an entry is the byte offset
 // of the neighbour's staged position, or its relative slot in a tile that does
-// not fit, and the last word is filled up with the staged particle far away.
+// not fit and without trange, and the last word is filled up with the staged particle far away.
 // Lists, counts and lane_slot of a staged tile are dealt to the lanes of the
 // force pass: first the particles that may have a neighbour across the periodic
 // edge, then the others, each by list length, longest first.  A wave runs as many
@@ -3157,7 +3157,8 @@ hipError_t launch_rebuild(lj_md* md, hipStream_t st) {
                        (const int*)md->perm, (const int*)md->permid, S, b,
                        md->variant != 3 || md->trange ? md->cellof : nullptr);
     // the tile lists take entries by cell and index within the cell, the
-    // one-step kernel staged indices, the block-per-replica kernel slot offsets
+    // one-step kernel words of staged offsets (or of slot offsets, where
+    // trange is not laid out), the block-per-replica kernel slot offsets
     auto lists = [&](auto kernel, int grid, int bs) {
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(bs), 0, st, (const double2*)b.pos_n, (const int*)md->cs,
                            (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, md->BS, S, md->maxnb, md->nbl, md->nbc,
@@ -3630,7 +3631,7 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
             md->resident = md->res_rows >= std::max(8.0, std::min((double)md->maxnb, mean_max + 4.0 * std::sqrt(mean_max)));
         }
         if (md->resident) {
-            // its lists are those of the one-step kernel, its cells those of every kernel
+            // one step kernel for all its steps, lists of slot offsets
             md->two_step = md->three_step = false;
             md->npt = 0;
             auto allow = [&](const void* k) { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kResLds); };
