@@ -158,7 +158,9 @@ mdlg_status lj_md_cg_detach(lj_md* md);
  *   v += dt/2 F(x); x += dt v; wrap; v += dt/2 F(x)
  * The library keeps the half-step velocity between steps and completes it at
  * the start of the next step, which is the same sequence of operations.
- * Repeated chunks are replayed from captured HIP graphs. */
+ * Repeated chunks are replayed from captured HIP graphs; replicas that one block
+ * each takes through the call (fuse_steps 0) need none: a launch covers up to
+ * 4096 steps. */
 mdlg_status lj_md_step(lj_md* md, int64_t nsteps, void* stream);
 
 /* Advance the replicas by nunits x rebuild_every MD steps like lj_md_step,
@@ -177,7 +179,9 @@ mdlg_status lj_md_step(lj_md* md, int64_t nsteps, void* stream);
  * or graphs behind each.  The graphs stay in the handle for later calls;
  * sampled units up to the last capture of this call warm up (capture
  * leaves the GPU idle) and are not counted.  nunits >= 3, sample_every in
- * [1, nunits / 3] (above 1 only with graph replay).  Synchronises `stream`. */
+ * [1, nunits / 3] (above 1 only with graph replay).  With one block per replica
+ * the three parts of a sampled unit are launches instead of graphs.
+ * Synchronises `stream`. */
 mdlg_status lj_md_step_timed(lj_md* md, int64_t nunits, int32_t sample_every, double* ms_out, int32_t* n_out,
                              void* stream);
 
