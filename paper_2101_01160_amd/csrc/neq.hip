@@ -184,6 +184,9 @@ __global__ __launch_bounds__(kNeqEventBS) void k_neq_event(const double2* __rest
             }
         }
     }
+    // Every wave waits until its own stores have arrived: neither the barrier
+    // nor the release below, which is one wave's, waits for those of the others.
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
