@@ -23,15 +23,15 @@
 #include <cmath>
 #include <vector>
 
+#include "hist_shares.h"
 #include "mdlg_internal.h"
 
 namespace mdlg {
 namespace {
 
-constexpr int kHistBS = 512;
+constexpr int kHistBS = kHistItem;
 constexpr int kHistMaxLags = 64;
 constexpr int kHistMaxSnap = 1 << 24;
-constexpr int kHistTargetBlocks = 512;   // blocks of a launch aimed at: two per compute unit
 constexpr int kHistReps = 32;            // replicas of one launch
 constexpr int kHistU = 4;                // work items of a thread in flight
 constexpr int kHistCopyLds = 16 * 1024;  // LDS that copies of the histograms may take
@@ -149,15 +149,14 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
         lmin = lags[s] < lmin ? lags[s] : lmin;
     }
     if (offsets[0] != 0) return fail(MDLG_EINVAL, std::string(who) + "offsets[0] must be 0");
-    long long n_max = 0, groups = 0;
+    long long groups = 0;
     for (int r = 0; r < n_rep; ++r) {
         const long long n = offsets[r + 1] - offsets[r];
         if (n < 0) return fail(MDLG_EINVAL, std::string(who) + "offsets must be non-decreasing");
         if (!(box_l[r] > 0.0) || !std::isfinite(box_l[r])) return fail(MDLG_EINVAL, std::string(who) + "box_l must be > 0");
-        n_max = std::max(n_max, n);
         groups += (n + 255) / 256;
     }
-    if (n_max == 0) return MDLG_OK;  // no particles, nothing to add
+    if (groups == 0) return MDLG_OK;  // no particles, nothing to add
     if (groups >= (1LL << 24))
         return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
     hipStream_t st = (hipStream_t)stream;
@@ -183,10 +182,10 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
         for (int r = 0; r <= nr; ++r) a.offset[r] = offsets[r0 + r];
         for (int r = 0; r < nr; ++r) a.box[r] = box_l[r0 + r];
         a.hist = (unsigned long long*)hist + (size_t)r0 * n_lag * nb2;
-        // shares: about kHistTargetBlocks blocks, none without work, none with 2^24 items (2^32 counts)
-        const long long items = (n_max + kHistBS - 1) / kHistBS * (n_snap - lmin);
-        const long long want = std::max((long long)kHistTargetBlocks / (nr * n_lag), items >> 23);
-        const unsigned nx = (unsigned)std::max(1LL, std::min(want, items));
+        long long items[kHistReps], shares[kHistReps];
+        for (int r = 0; r < nr; ++r) items[r] = (offsets[r0 + r + 1] - offsets[r0 + r] + kHistBS - 1) / kHistBS * (n_snap - lmin);
+        hist_deal(nr, items, n_lag, shares);
+        const unsigned nx = (unsigned)shares[0];
         hipLaunchKernelGGL(k_disp_hist, dim3(nx, (unsigned)n_lag, (unsigned)nr), dim3(kHistBS), lds, st, a);
         e = hipGetLastError();
     }
