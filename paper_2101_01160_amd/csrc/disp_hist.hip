@@ -43,6 +43,8 @@ struct HistArgs {
     int n_snap, n_bin, n_lag, copies;
     double half;                               // n_bin / 2
     unsigned long long* __restrict__ hist;     // [replicas of the launch][n_lag][2][n_bin + 2]
+    int n_rep;                                 // replicas of the launch
+    int b0[kHistReps + 1];                     // replica r has blocks b0[r] .. b0[r + 1] - 1
     long long offset[kHistReps + 1];
     double box[kHistReps];
     int lags[kHistMaxLags];
@@ -68,13 +70,20 @@ __global__ __launch_bounds__(kHistBS) void k_disp_hist(HistArgs a) {
     extern __shared__ unsigned hl[];  // [2 (n_bin + 2)][copies]
     const int tid = threadIdx.x;
     const int nb2 = 2 * (a.n_bin + 2);
-    const int s = blockIdx.y, r = blockIdx.z, l = a.lags[s];
+    const int s = blockIdx.y, l = a.lags[s];
+    int r = 0, hi = a.n_rep;  // b0[r] <= blockIdx.x < b0[hi]
+    while (hi - r > 1) {
+        const int mid = (r + hi) / 2;
+        if (a.b0[mid] <= (int)blockIdx.x) r = mid;
+        else hi = mid;
+    }
+    const int share = (int)blockIdx.x - a.b0[r], shares = a.b0[r + 1] - a.b0[r];
     const long long j0 = a.offset[r];
     const long long n = a.offset[r + 1] - j0;
     const int npair = a.n_snap - l;
     // this block's share of the items: group i / npair of kHistBS particles, pair i % npair
     const long long items = (n + kHistBS - 1) / kHistBS * npair;
-    const long long i0 = items * blockIdx.x / gridDim.x, i1 = items * (blockIdx.x + 1LL) / gridDim.x;
+    const long long i0 = items * share / shares, i1 = items * (share + 1LL) / shares;
     if (i0 >= i1) return;  // uniform over the block
     for (int i = tid; i < nb2 * a.copies; i += kHistBS) hl[i] = 0u;
     __syncthreads();
@@ -185,8 +194,10 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
         long long items[kHistReps], shares[kHistReps];
         for (int r = 0; r < nr; ++r) items[r] = (offsets[r0 + r + 1] - offsets[r0 + r] + kHistBS - 1) / kHistBS * (n_snap - lmin);
         hist_deal(nr, items, n_lag, shares);
-        const unsigned nx = (unsigned)shares[0];
-        hipLaunchKernelGGL(k_disp_hist, dim3(nx, (unsigned)n_lag, (unsigned)nr), dim3(kHistBS), lds, st, a);
+        a.n_rep = nr;
+        for (int r = 0; r < nr; ++r) a.b0[r + 1] = a.b0[r] + (int)shares[r];
+        if (a.b0[nr] == 0) continue;  // no particles in these replicas
+        hipLaunchKernelGGL(k_disp_hist, dim3((unsigned)a.b0[nr], (unsigned)n_lag), dim3(kHistBS), lds, st, a);
         e = hipGetLastError();
     }
     const hipError_t es = hipStreamSynchronize(st);

@@ -14,13 +14,19 @@ constexpr long long kHistBlockItems = 1LL << 22;  // items of one block at most
 constexpr int kHistTargetBlocks = 512;            // blocks of a launch aimed at: two per compute unit
 
 // shares[r]: blocks of replica r for each of n_lag lags, where it has items[r]
-// items; every replica of the launch gets what the largest one needs.
+// items: its part of the blocks aimed at, by its items.  (With as many for each
+// replica, 16 blocks were left for the large one of 2^20 particles among 31 of
+// 4096: 522 us for 9 snapshots and one lag, 18.3 ms for 20 and 16 lags.)
 inline void hist_deal(int n_rep, const long long* items, int n_lag, long long* shares) {
-    long long most = 0;
-    for (int r = 0; r < n_rep; ++r) most = std::max(most, items[r]);
-    const long long target = kHistTargetBlocks / ((long long)n_rep * n_lag);
-    const long long least = (most + kHistBlockItems - 1) / kHistBlockItems;
-    for (int r = 0; r < n_rep; ++r) shares[r] = std::max({1LL, least, std::min(target, most)});
+    long long total = 0;
+    for (int r = 0; r < n_rep; ++r) total += items[r];
+    const long long target = std::max(1, kHistTargetBlocks / n_lag);
+    for (int r = 0; r < n_rep; ++r) {
+        // target * items[r] / total, of at most 2^9 * 2^47
+        const long long part = total > 0 ? target * items[r] / total : 0;
+        const long long least = (items[r] + kHistBlockItems - 1) / kHistBlockItems;  // 0 without items
+        shares[r] = std::max(least, std::min(part, items[r]));
+    }
 }
 
 }  // namespace mdlg

@@ -51,3 +51,18 @@ def test_no_block_counts_to_2_32(rule, n_rep, n_lag, most):
 
 def test_replicas_without_particles(rule):
     assert (rule([0, 7, 0], 2) >= 0).all()
+
+
+@pytest.mark.parametrize("items,n_lag", [([18000] + [64] * 31, 1), ([64] * 31 + [18000], 16), ([18000, 0, 0, 1], 4),
+                                         ([5, 3], 64), ([2**23 - 1] + [8] * 255, 1)])
+def test_blocks_follow_the_work(rule, items, n_lag):
+    """The launch has about 512 blocks, and no replica is left with much more work per block than all have together;
+    one without work has none."""
+    shares = rule(items, n_lag)
+    target = max(1, 512 // n_lag)
+    assert shares.sum() <= target + len(items)
+    for n, k in zip(items, shares):
+        assert (k == 0) == (n == 0)
+        if k:
+            # floor(target n / total) + 1 > target n / total, so the items of a block stay below twice the average
+            assert -(-n // int(k)) <= max(2 * sum(items) // target, 1) + 1
