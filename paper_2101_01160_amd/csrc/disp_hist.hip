@@ -17,10 +17,12 @@
 // bin.  About 512 blocks in all keep those few: with a block per 256 particles
 // and chunk of pairs the 890,000 global atomics of 4 x 99,856 particles, 8 pairs
 // and 96 bins took most of 33 us; 17.7 us here (20.6 us with 1024 blocks of half
-// the threads).  The tables of a call travel as kernel arguments: no allocation
-// and no copy, which with the wait for them took half of its 81 us (40 us now).
+// the threads).  The tables of up to 512 replicas travel as kernel arguments: no
+// allocation and no copy, which with the wait for them took half of its 81 us (40
+// us now).
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "hist_shares.h"
@@ -32,7 +34,8 @@ namespace {
 constexpr int kHistBS = kHistItem;
 constexpr int kHistMaxLags = 64;
 constexpr int kHistMaxSnap = 1 << 24;
-constexpr int kHistReps = 32;            // replicas of one launch
+constexpr int kHistReps = 128;           // replicas of a launch whose tables travel as kernel arguments
+constexpr int kHistLaunches = 4;         // such launches of a call at most
 constexpr int kHistU = 4;                // work items of a thread in flight
 constexpr int kHistCopyLds = 16 * 1024;  // LDS that copies of the histograms may take
 
@@ -42,13 +45,34 @@ struct HistArgs {
     long long n_tot;
     int n_snap, n_bin, n_lag, copies;
     double half;                               // n_bin / 2
-    unsigned long long* __restrict__ hist;     // [replicas of the launch][n_lag][2][n_bin + 2]
-    int n_rep;                                 // replicas of the launch
-    int b0[kHistReps + 1];                     // replica r has blocks b0[r] .. b0[r + 1] - 1
-    long long offset[kHistReps + 1];
-    double box[kHistReps];
+    unsigned long long* __restrict__ hist;     // [n_rep][n_lag][2][n_bin + 2]
+    int n_rep;
     int lags[kHistMaxLags];
     double inv_h[kHistMaxLags];                // 1 / h
+};
+
+// The replicas, replica r with blocks b0[r] .. b0[r + 1] - 1: as kernel
+// arguments, or in device memory.
+struct HistReps {
+    int b0[kHistReps + 1];
+    long long offset[kHistReps + 1];
+    double box[kHistReps];
+    __device__ __forceinline__ int rep(int b, int n_rep) const {
+        int r = 0, hi = n_rep;  // b0[r] <= b < b0[hi]
+        while (hi - r > 1) {
+            const int mid = (r + hi) / 2;
+            if (b0[mid] <= b) r = mid;
+            else hi = mid;
+        }
+        return r;
+    }
+};
+struct HistTable {
+    const long long* offset;
+    const double* box;
+    const int* b0;
+    const int* rep_of;  // the replica of each block (a search costs a memory latency per halving)
+    __device__ __forceinline__ int rep(int b, int) const { return rep_of[b]; }
 };
 
 __device__ __forceinline__ double box_delta(double xc, double xp, int di, double L) {
@@ -66,28 +90,24 @@ __device__ __forceinline__ int disp_bin(double d, double inv_h, double half, int
     return t < 0.0 ? n_bin : n_bin + 1;
 }
 
-__global__ __launch_bounds__(kHistBS) void k_disp_hist(HistArgs a) {
+template <typename Reps>
+__global__ __launch_bounds__(kHistBS) void k_disp_hist(HistArgs a, Reps t) {
     extern __shared__ unsigned hl[];  // [2 (n_bin + 2)][copies]
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, BS = blockDim.x;
     const int nb2 = 2 * (a.n_bin + 2);
     const int s = blockIdx.y, l = a.lags[s];
-    int r = 0, hi = a.n_rep;  // b0[r] <= blockIdx.x < b0[hi]
-    while (hi - r > 1) {
-        const int mid = (r + hi) / 2;
-        if (a.b0[mid] <= (int)blockIdx.x) r = mid;
-        else hi = mid;
-    }
-    const int share = (int)blockIdx.x - a.b0[r], shares = a.b0[r + 1] - a.b0[r];
-    const long long j0 = a.offset[r];
-    const long long n = a.offset[r + 1] - j0;
+    const int r = t.rep(blockIdx.x, a.n_rep);
+    const int share = (int)blockIdx.x - t.b0[r], shares = t.b0[r + 1] - t.b0[r];
+    const long long j0 = t.offset[r];
+    const long long n = t.offset[r + 1] - j0;
     const int npair = a.n_snap - l;
-    // this block's share of the items: group i / npair of kHistBS particles, pair i % npair
-    const long long items = (n + kHistBS - 1) / kHistBS * npair;
+    // this block's share of the items: group i / npair of BS particles, pair i % npair
+    const long long items = (n + BS - 1) / BS * npair;
     const long long i0 = items * share / shares, i1 = items * (share + 1LL) / shares;
     if (i0 >= i1) return;  // uniform over the block
-    for (int i = tid; i < nb2 * a.copies; i += kHistBS) hl[i] = 0u;
+    for (int i = tid; i < nb2 * a.copies; i += BS) hl[i] = 0u;
     __syncthreads();
-    const double L = a.box[r], inv = a.inv_h[s];
+    const double L = t.box[r], inv = a.inv_h[s];
     unsigned* hx = hl + tid % a.copies;
     unsigned* hy = hx + (a.n_bin + 2) * a.copies;
     long long g = i0 / npair;
@@ -98,7 +118,7 @@ __global__ __launch_bounds__(kHistBS) void k_disp_hist(HistArgs a) {
         bool on[kHistU];
 #pragma unroll
         for (int u = 0; u < kHistU; ++u) {
-            const long long j = g * kHistBS + tid;
+            const long long j = g * BS + tid;
             on[u] = i + u < i1 && j < n;
             if (on[u]) {
                 const long long at = (long long)q * a.n_tot + j0 + j, to = at + l * a.n_tot;
@@ -123,7 +143,7 @@ __global__ __launch_bounds__(kHistBS) void k_disp_hist(HistArgs a) {
     }
     __syncthreads();
     unsigned long long* out = a.hist + ((long long)r * a.n_lag + s) * nb2;
-    for (int i = tid; i < nb2; i += kHistBS) {
+    for (int i = tid; i < nb2; i += BS) {
         unsigned c = 0u;
         for (int k = 0; k < a.copies; ++k) c += hl[i * a.copies + k];
         if (c) atomicAdd(out + i, (unsigned long long)c);
@@ -185,23 +205,65 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
         a.inv_h[s] = inv_h[s];
     }
     const size_t lds = sizeof(unsigned) * (size_t)nb2 * a.copies;  // at most 32 KB
-    hipError_t e = hipSuccess;
-    for (int r0 = 0; r0 < n_rep && e == hipSuccess; r0 += kHistReps) {
-        const int nr = std::min(kHistReps, n_rep - r0);
-        for (int r = 0; r <= nr; ++r) a.offset[r] = offsets[r0 + r];
-        for (int r = 0; r < nr; ++r) a.box[r] = box_l[r0 + r];
-        a.hist = (unsigned long long*)hist + (size_t)r0 * n_lag * nb2;
-        long long items[kHistReps], shares[kHistReps];
-        for (int r = 0; r < nr; ++r) items[r] = (offsets[r0 + r + 1] - offsets[r0 + r] + kHistBS - 1) / kHistBS * (n_snap - lmin);
+    // threads of a block, the particles of a work item: those of a replica, if they are fewer than kHistBS on average
+    // (5000 replicas of 64 particles, 9 snapshots and one lag: 45 us with 512, 19 with 64)
+    int lg = 6;
+    while ((1 << lg) < kHistBS && (1 << lg) < a.n_tot / n_rep) ++lg;
+    const int BS = 1 << lg;
+    // Launches of up to kHistReps replicas, or one with a table in device memory
+    // where they would be more than kHistLaunches: the table's allocation and copy
+    // cost 30 us and more.  (A launch for every 32 replicas took 218 us for 1024 of
+    // 512 particles, 9 snapshots and one lag, and 800 us for 5000 of 64.)
+    const bool table = n_rep > kHistReps * kHistLaunches;
+    const int per = table ? n_rep : std::min(n_rep, kHistReps);
+    std::vector<long long> work(2 * (size_t)per);  // items, then shares
+    long long *items = work.data(), *shares = items + per;
+    auto deal = [&](int r0, int nr, int* b0) {
+        for (int r = 0; r < nr; ++r) items[r] = ((offsets[r0 + r + 1] - offsets[r0 + r] + BS - 1) >> lg) * (n_snap - lmin);
         hist_deal(nr, items, n_lag, shares);
-        a.n_rep = nr;
-        for (int r = 0; r < nr; ++r) a.b0[r + 1] = a.b0[r] + (int)shares[r];
-        if (a.b0[nr] == 0) continue;  // no particles in these replicas
-        hipLaunchKernelGGL(k_disp_hist, dim3((unsigned)a.b0[nr], (unsigned)n_lag), dim3(kHistBS), lds, st, a);
+        b0[0] = 0;
+        for (int r = 0; r < nr; ++r) b0[r + 1] = b0[r] + (int)shares[r];
+        return dim3((unsigned)b0[nr], (unsigned)n_lag);
+    };
+    hipError_t e = hipSuccess;
+    void* dev = nullptr;
+    std::vector<unsigned char> host;  // outlives its copy
+    if (table) {
+        const size_t off_box = sizeof(long long) * ((size_t)n_rep + 1), off_b0 = off_box + sizeof(double) * n_rep,
+                     off_rep = off_b0 + sizeof(int) * ((size_t)n_rep + 1);
+        host.resize(off_rep);
+        std::memcpy(host.data(), offsets, off_box);
+        std::memcpy(host.data() + off_box, box_l, sizeof(double) * n_rep);
+        const dim3 grid = deal(0, n_rep, (int*)(host.data() + off_b0));
+        host.resize(off_rep + sizeof(int) * grid.x);
+        int *b0 = (int*)(host.data() + off_b0), *rep_of = (int*)(host.data() + off_rep);
+        for (int r = 0; r < n_rep; ++r) std::fill(rep_of + b0[r], rep_of + b0[r + 1], r);
+        a.n_rep = n_rep;
+        a.hist = (unsigned long long*)hist;
+        MDLG_HIP(hipMallocAsync(&dev, host.size(), st));
+        e = hipMemcpyAsync(dev, host.data(), host.size(), hipMemcpyHostToDevice, st);
+        const HistTable t{(const long long*)dev, (const double*)((const char*)dev + off_box),
+                          (const int*)((const char*)dev + off_b0), (const int*)((const char*)dev + off_rep)};
+        if (e == hipSuccess) {
+            hipLaunchKernelGGL(k_disp_hist<HistTable>, grid, dim3(BS), lds, st, a, t);
+            e = hipGetLastError();
+        }
+    }
+    for (int r0 = 0; r0 < n_rep && !table && e == hipSuccess; r0 += per) {
+        HistReps t{};
+        a.n_rep = std::min(per, n_rep - r0);
+        a.hist = (unsigned long long*)hist + (size_t)r0 * n_lag * nb2;
+        const dim3 grid = deal(r0, a.n_rep, t.b0);
+        if (grid.x == 0) continue;  // no particles in these replicas
+        std::copy_n(offsets + r0, a.n_rep + 1, t.offset);
+        std::copy_n(box_l + r0, a.n_rep, t.box);
+        hipLaunchKernelGGL(k_disp_hist<HistReps>, grid, dim3(BS), lds, st, a, t);
         e = hipGetLastError();
     }
     const hipError_t es = hipStreamSynchronize(st);
+    const hipError_t ef = dev ? hipFreeAsync(dev, st) : hipSuccess;
     MDLG_HIP(e);
     MDLG_HIP(es);
+    MDLG_HIP(ef);
     return MDLG_OK;
 }

@@ -20,10 +20,9 @@ constexpr int kHistTargetBlocks = 512;            // blocks of a launch aimed at
 inline void hist_deal(int n_rep, const long long* items, int n_lag, long long* shares) {
     long long total = 0;
     for (int r = 0; r < n_rep; ++r) total += items[r];
-    const long long target = std::max(1, kHistTargetBlocks / n_lag);
+    const double scale = total > 0 ? std::max(1, kHistTargetBlocks / n_lag) / (double)total : 0.0;
     for (int r = 0; r < n_rep; ++r) {
-        // target * items[r] / total, of at most 2^9 * 2^47
-        const long long part = total > 0 ? target * items[r] / total : 0;
+        const long long part = (long long)((double)items[r] * scale);
         const long long least = (items[r] + kHistBlockItems - 1) / kHistBlockItems;  // 0 without items
         shares[r] = std::max(least, std::min(part, items[r]));
     }

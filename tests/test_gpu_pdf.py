@@ -79,6 +79,18 @@ def test_several_launches_and_shares(n_rep, n_bin):
     assert np.array_equal(got, omd.displacement_hist_series(off, box, xs, imgs, lags, h, n_bin))
 
 
+@pytest.mark.parametrize("n_rep,sizes", [(129, (511, 0, 513)), (513, (64, 65, 1, 0, 63)), (600, (128, 100)),
+                                         (700, (257, 0, 300)), (514, (0,) * 513 + (900,))])
+def test_many_replicas(n_rep, sizes):
+    """One launch after another with tables as kernel arguments (to 512 replicas), one launch with tables in device
+    memory (more); blocks of one to eight waves by the mean size, some replicas empty."""
+    xs, imgs, off = batch([(sizes[r % len(sizes)], 10.0 + r % 7, 0.8) for r in range(n_rep)], 4, seed=n_rep)
+    box = [10.0 + r % 7 for r in range(n_rep)]
+    lags, h, n_bin = [1, 3], [0.3, 0.5], 24
+    got = gpu_hist(off, box, xs, imgs, lags, h, n_bin)
+    assert np.array_equal(got, omd.displacement_hist_series(off, box, xs, imgs, lags, h, n_bin))
+
+
 @pytest.mark.parametrize("n_bin", [1, 2, 4094])
 def test_bin_count_extremes(n_bin):
     specs = [(700, 20.0, 1.0), (129, 33.0, 0.4)]
