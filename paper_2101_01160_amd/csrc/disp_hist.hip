@@ -220,7 +220,7 @@ extern "C" mdlg_status mdlg_displacement_hist(int32_t n_rep, const int64_t* offs
     long long *items = work.data(), *shares = items + per;
     auto deal = [&](int r0, int nr, int* b0) {
         for (int r = 0; r < nr; ++r) items[r] = ((offsets[r0 + r + 1] - offsets[r0 + r] + BS - 1) >> lg) * (n_snap - lmin);
-        hist_deal(nr, items, n_lag, shares);
+        hist_deal(nr, items, n_lag, shares, BS);
         b0[0] = 0;
         for (int r = 0; r < nr; ++r) b0[r + 1] = b0[r] + (int)shares[r];
         return dim3((unsigned)b0[nr], (unsigned)n_lag);
