@@ -39,10 +39,11 @@ struct CgArgs {
 // the destination cell modulo lx.
 __device__ __forceinline__ int lattice_move(double t0, int i0, double t1, int i1, int lx, int& cell) {
     const double f0 = floor(t0), f1 = floor(t1);
-    const int di = (int)((unsigned)i1 - (unsigned)i0);
+    int di;
+    const bool near = image_step(i0, i1, di);
     // |t| < 2^26 by the high words of both (a NaN is larger): 32 bits hold it all (lx <= 46340)
     if (max((unsigned)__double2hiint(t0) & 0x7fffffffu, (unsigned)__double2hiint(t1) & 0x7fffffffu) < 0x41900000u &&
-        (unsigned)(di + 1000) <= 2000u) {
+        near) {
         const int q = (int)f1;
         cell = q;
         if ((unsigned)q >= (unsigned)lx) {

@@ -65,6 +65,12 @@ __device__ __forceinline__ double wave_sum(double v) {
     return v;
 }
 
+// The difference of two image counts, and whether it is at most 1000 boxes
+// either way (where it also has not left the 32-bit range).
+__device__ __forceinline__ bool image_step(int i0, int i1, int& di) {
+    return !__builtin_sub_overflow(i1, i0, &di) && (unsigned)(di + 1000) <= 2000u;
+}
+
 // Lattice coordinate floor((x + shift) * inv), every operation rounded once,
 // exactly as written (no fused multiply-add), so that host and device agree
 // on the cell of a position bit for bit.

@@ -55,9 +55,10 @@ __device__ __forceinline__ long long cell_of(double x, double inv) {
 __device__ __forceinline__ int move_at(double x0, int i0, double x1, int i1, double inv, int lx, int& cell) {
 #pragma clang fp contract(off)
     const double t0 = x0 * inv, t1 = x1 * inv;
-    const int di = (int)((unsigned)i1 - (unsigned)i0);
+    int di;
+    const bool near = image_step(i0, i1, di);
     // 0 <= t < 2^26 by the high words of both (a set sign or a NaN is larger)
-    if (max((unsigned)__double2hiint(t0), (unsigned)__double2hiint(t1)) < 0x41900000u && (unsigned)(di + 1000) <= 2000u) {
+    if (max((unsigned)__double2hiint(t0), (unsigned)__double2hiint(t1)) < 0x41900000u && near) {
         // in 32 bits, as the long form would give it (lx <= 46340: below 2^29);
         // truncation is the floor here
         const int q = (int)t1;

@@ -77,6 +77,33 @@ def test_block_limit_and_wide_coordinates(n, shift, k):
     compare(lx, L, x0, x1, i0, i1, k0=k, k1=k + 1, u=(0.25, -0.125) if k else (0.0, 0.0))
 
 
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_image_counts_at_the_ends_of_their_range(noalloc):
+    """Image counts whose difference leaves 32 bits are an overflow event, also where a particle crosses the box edge and
+    what 32 bits leave of the difference is that crossing; with the same large images at both ends particles move as
+    ever."""
+    import torch
+
+    import paper_2101_01160_amd as m
+    n, lx, L = 3000, 20, 40.0
+    rng = np.random.default_rng(5)
+    x0, x1, i0, i1 = src.gaussian_step(rng, n, L, var=(0.8 * L / lx) ** 2)
+    lo, hi = -2**31, 2**31 - 1
+    i0, i1 = i0.copy(), i1.copy()
+    x0[0::9], x1[0::9] = rng.uniform(L - 2.0, L, x0[0::9].shape), rng.uniform(0.0, 2.0, x0[0::9].shape)
+    x0[1::9], x1[1::9] = rng.uniform(0.0, 2.0, x0[1::9].shape), rng.uniform(L - 2.0, L, x0[1::9].shape)
+    for k, (a, b) in enumerate(((hi, lo), (lo, hi), (hi - 500, lo + 400), (lo + 3, hi - 7), (hi, hi), (lo, lo))):
+        i0[k::9], i1[k::9] = a, b
+    counts = torch.zeros(50, dtype=torch.int64, device="cuda")
+    acc = torch.zeros((49, lx, lx), dtype=torch.int32, device="cuda")
+    m.mdlg_coarse_grain(lx, L, _cuda(x0), _cuda(x1), counts, None, _cuda(i0, torch.int32), _cuda(i1, torch.int32),
+                        cell_acc=acc, noalloc=noalloc)
+    torch.cuda.synchronize()
+    co, no, _ = omd.coarse_grain(lx, L, x0, x1, i0, i1, dense=True)
+    assert np.array_equal(counts.cpu().numpy(), co) and np.array_equal(acc.cpu().numpy(), no)
+    assert co[49] >= 4 * (n // 9)
+
+
 def test_images_and_frame_shift():
     rng = np.random.default_rng(2)
     lx, L, n = 50, 100.0, 50_000

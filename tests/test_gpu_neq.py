@@ -83,6 +83,24 @@ def test_cell_edges_and_box_side():
     assert o.sum() > 0
 
 
+@pytest.mark.parametrize("n", [500, 60001])
+def test_image_counts_at_the_ends_of_their_range(n):
+    """Image counts whose difference leaves 32 bits are overflow events, also where a particle crosses the box edge and
+    what 32 bits leave of the difference is that crossing (global atomics, and counters in LDS)."""
+    lx, P = 10, 18
+    L = 2.0 * lx
+    pos, img = walk(n, L, P, 1.0, seed=3)
+    lo, hi = -2**31, 2**31 - 1
+    pos[::2, :50], pos[1::2, :50] = L - 0.5, 0.5
+    img[::2, :50], img[1::2, :50] = hi, lo
+    img[::2, 50:100], img[1::2, 50:100] = lo + 4, hi - 9
+    img[:, 100:150], img[:, 150:200] = lo, hi
+    f, o, x = gpu(L, lx, pos, img)
+    rf, ro, rx = omd.neq_mdlg(lx, L, [0, n], pos, img)
+    assert np.array_equal(f, rf) and np.array_equal(o, ro) and np.array_equal(x, rx)
+    assert (ro >= 100).all()
+
+
 def test_shear_wave_md_ensemble_matches_oracle():
     import torch
 
