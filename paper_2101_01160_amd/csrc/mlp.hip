@@ -23,7 +23,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kIn = 6, kHid = 256, kOut = 49, kOutP = 64;
 constexpr long kW1 = 0, kB1 = 1536, kW2 = 1792, kB2 = 67328, kW3 = 67584, kB3 = 133120, kW4 = 133376, kB4 = 145920;
 constexpr long kParams = 145969;
-constexpr int kMaxSplit = 16;
+constexpr int kMaxSplit = 32, kMidSplit = 16;  // splits of the batch for gradients: layers 1 and 4, layers 2 and 3
 // Fixed input map of x = (phi, kT, dt_cg/dx, |u|, cos, sin): phi / 0.4,
 // ln kT / ln 20, (ln(dt_cg/dx) + 6) / 1.5, and the drift as the vector
 // 5 |u| (cos, sin) with its length 5 |u|; fp32, every operation rounded once.
@@ -315,11 +315,20 @@ __global__ __launch_bounds__(kTrainBS) __attribute__((amdgpu_waves_per_eu(2))) v
 constexpr int kTK = 32;            // k step, and the padding of the samples
 constexpr int kWgTiles = 4 + 16 + 16 + 4;
 
-__global__ __launch_bounds__(256) void k_train_wgrad(TrainBufs t, int chunk, float* __restrict__ part) {
+// Splits of a training batch: k steps of a split and how many there are, for
+// layers 1 and 4 and for layers 2 and 3.
+struct Splits {
+    int chunk, n, chunk_mid, n_mid;
+};
+
+__global__ __launch_bounds__(256) void k_train_wgrad(TrainBufs t, Splits sp, float* __restrict__ part) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int lr = lane & 15, lq = lane >> 4;
     // the tile's layer: inputs A [M rows], gradients G [N rows], output W [M][N] and bias [N]
     int tile = blockIdx.x, M = kHid, N = kHid, last = kHid / 16 - 1;
+    const bool mid = tile >= 4 && tile < 36;
+    if (mid && (int)blockIdx.y >= sp.n_mid) return;
+    const int chunk = mid ? sp.chunk_mid : sp.chunk;
     const bf16 *A, *G;
     long ow, ob;
     if (tile < 4) {
@@ -390,7 +399,7 @@ __global__ __launch_bounds__(256) void k_train_wgrad(TrainBufs t, int chunk, flo
 // the update of the fp32 master weights and their bf16 copies; without, the
 // gradient itself.  The last block adds the samples' losses up (fixed order).
 template <bool ADAM>
-__global__ __launch_bounds__(256) void k_train_sum(const float* __restrict__ part, int splits,
+__global__ __launch_bounds__(256) void k_train_sum(const float* __restrict__ part, Splits sp,
                                                    const float* __restrict__ loss_b, int B, float* __restrict__ loss,
                                                    float* __restrict__ grad, float* __restrict__ w, float* __restrict__ m,
                                                    float* __restrict__ v, float lr, float b1, float b2, float eps,
@@ -407,6 +416,7 @@ __global__ __launch_bounds__(256) void k_train_sum(const float* __restrict__ par
     }
     const long i = (long)blockIdx.x * 256 + threadIdx.x;
     if (i >= kParams) return;
+    const int splits = i >= kW2 && i < kW4 ? sp.n_mid : sp.n;  // the same for a whole block
     float gi = 0.f;
     for (int z0 = 0; z0 < splits; z0 += 8) {
         float p[8];
@@ -620,21 +630,28 @@ TrainBufs train_bufs(const mdlg_mlp* m, int B) {
     return t;
 }
 
-// Forward, backward and the gradient's partials; *splits receives their number.
-hipError_t gradient_partials(mdlg_mlp* m, const float* x, const float* R, int B, int* splits, hipStream_t st) {
+// Forward, backward and the gradient's partials; *sp receives their splits.
+hipError_t gradient_partials(mdlg_mlp* m, const float* x, const float* R, int B, Splits* sp, hipStream_t st) {
     const TrainBufs t = train_bufs(m, B);
     hipLaunchKernelGGL(k_train_fb, dim3((unsigned)(t.steps * kTK / kTB)), dim3(kTrainBS), 0, st, x, R, B, (const float*)m->w,
                        (const bf16*)m->wc, t, m->loss_b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // at least eight k steps in each of a power of two of splits, up to 16 (40
-    // tiles x 8 splits are a block or two per compute unit: for 2048 samples 16
-    // splits made the products and the sums 0.6 and 0.9 us longer)
-    int want = 1;
-    while (2 * want <= kMaxSplit && B >= 16 * want * kTK) want *= 2;
-    const int steps = (B + kTK - 1) / kTK, chunk = (steps + want - 1) / want;
-    *splits = (int)((t.steps + chunk - 1) / chunk);
-    hipLaunchKernelGGL(k_train_wgrad, dim3(kWgTiles, (unsigned)*splits), dim3(256), 0, st, t, chunk, m->part);
+    // at least eight k steps in each of a power of two of splits: shorter FP32
+    // chains, and enough blocks.  Up to 16 for layers 2 and 3, whose 32 tiles
+    // then are two blocks per compute unit (40 tiles x 8 splits for 2048 samples:
+    // 16 made the products and the sums 0.6 and 0.9 us longer), up to 32 for the
+    // eight tiles of layers 1 and 4.
+    auto split = [&](int most, int* n) {
+        int want = 1;
+        while (2 * want <= most && B >= 16 * want * kTK) want *= 2;
+        const int chunk = ((int)t.steps + want - 1) / want;
+        *n = ((int)t.steps + chunk - 1) / chunk;
+        return chunk;
+    };
+    sp->chunk = split(kMaxSplit, &sp->n);
+    sp->chunk_mid = split(kMidSplit, &sp->n_mid);
+    hipLaunchKernelGGL(k_train_wgrad, dim3(kWgTiles, (unsigned)sp->n), dim3(256), 0, st, t, *sp, m->part);
     return hipGetLastError();
 }
 
@@ -728,9 +745,9 @@ extern "C" mdlg_status mdlg_mlp_gradient(mdlg_mlp* m, const float* x, const floa
     if (s != MDLG_OK) return s;
     if (!x || !target) return fail(MDLG_EINVAL, "mdlg_mlp_gradient: NULL argument");
     hipStream_t st = (hipStream_t)stream;
-    int splits = 0;
-    MDLG_HIP(gradient_partials(m, x, target, B, &splits, st));
-    hipLaunchKernelGGL(k_train_sum<false>, dim3(nblk(kParams) + 1), dim3(256), 0, st, (const float*)m->part, splits,
+    Splits sp{};
+    MDLG_HIP(gradient_partials(m, x, target, B, &sp, st));
+    hipLaunchKernelGGL(k_train_sum<false>, dim3(nblk(kParams) + 1), dim3(256), 0, st, (const float*)m->part, sp,
                        (const float*)m->loss_b, B, loss, grad, m->w, m->m, m->v, 0.f, 0.f, 0.f, 0.f, 1.f, 1.f, m->wc);
     MDLG_HIP(hipGetLastError());
     return MDLG_OK;
@@ -743,12 +760,12 @@ extern "C" mdlg_status mdlg_mlp_train_step(mdlg_mlp* m, const float* x, const fl
     if (!x || !target) return fail(MDLG_EINVAL, "mdlg_mlp_train_step: NULL argument");
     if (!(lr > 0.f) || !std::isfinite(lr)) return fail(MDLG_EINVAL, "mdlg_mlp_train_step: lr must be > 0");
     hipStream_t st = (hipStream_t)stream;
-    int splits = 0;
-    MDLG_HIP(gradient_partials(m, x, target, B, &splits, st));
+    Splits sp{};
+    MDLG_HIP(gradient_partials(m, x, target, B, &sp, st));
     m->step += 1;
     const float b1 = 0.9f, b2 = 0.999f;
     const float bc1 = 1.0f - std::pow(b1, (float)m->step), bc2 = 1.0f - std::pow(b2, (float)m->step);
-    hipLaunchKernelGGL(k_train_sum<true>, dim3(nblk(kParams) + 1), dim3(256), 0, st, (const float*)m->part, splits,
+    hipLaunchKernelGGL(k_train_sum<true>, dim3(nblk(kParams) + 1), dim3(256), 0, st, (const float*)m->part, sp,
                        (const float*)m->loss_b, B, loss, (float*)nullptr, m->w, m->m, m->v, lr, b1, b2, 1e-8f, bc1, bc2,
                        m->wc);
     MDLG_HIP(hipGetLastError());

@@ -123,6 +123,31 @@ def test_gradient_at_batch_edges(B):
         assert np.linalg.norm(g - r) <= 3e-2 * np.linalg.norm(r), name
 
 
+@pytest.mark.parametrize("B", [8192, 16384])
+def test_large_batches_keep_short_chains_in_layers_1_and_4(B):
+    """From 8192 samples the weight gradients of layers 1 and 4 are FP32 sums over 32 equal parts of the batch, then over
+    the parts.  One sample with targets 2^31 times the others' in part 0 and a part full of small ones: both parts' sums
+    are exact (equal samples, multiples of one bf16 value), so that the gradient is theirs added and rounded once.  In
+    one chain of half as many parts every small addend, 2^-26 of the sum in a k step, would be lost."""
+    theta = params(6)
+    part = B // 32
+    X = np.repeat(inputs(3, 1), B, axis=0)
+    row = targets(3, 1)[0]
+    big, small = np.zeros((B, 49)), np.zeros((B, 49))
+    big[0] = row
+    small[part:part + 256] = row * 2.0**-31
+    net = make(theta, B)
+    grads = []
+    for R in (big, small, big + small):
+        _, g = net.gradient(_t(X), _t(R))
+        grads.append(g.cpu().numpy())
+    for name in ("b1", "b4"):
+        a, b = next((a, b) for k, a, b in BLOCKS if k == name)
+        assert np.abs(grads[1][a:b]).max() > 0.0
+        assert np.array_equal(grads[2][a:b], grads[0][a:b] + grads[1][a:b]), name
+        assert not np.array_equal(grads[2][a:b], grads[0][a:b]), name
+
+
 def test_first_adam_step_is_lr_times_sign():
     import torch
     B, lr = 128, 1e-3
