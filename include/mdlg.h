@@ -173,14 +173,15 @@ mdlg_status lj_md_step(lj_md* md, int64_t nsteps, void* stream);
  * sampling keeps the timing's own cost small).  ms_out (host [3]) receives
  * the device time per launch of [0] an ordinary step kernel (the ordinary
  * steps' graph time over their number), [1] a coarse-graining step with
- * the launches after it in its unit (the last graph's time less its
- * ordinary steps, per event) and [2] a cell rebuild, each averaged over the
- * counted sampled units; n_out (host [3], may be NULL) the number of kernels
+ * the launches before and after it in the last graph (that graph's time per
+ * event) and [2] a cell rebuild, each averaged over the counted sampled units; n_out (host [3], may be NULL) the number of kernels
  * or graphs behind each.  The graphs stay in the handle for later calls;
  * sampled units up to the last capture of this call warm up (capture
  * leaves the GPU idle) and are not counted.  nunits >= 3, sample_every in
  * [1, nunits / 3] (above 1 only with graph replay).  With one block per replica
- * the three parts of a sampled unit are launches instead of graphs.
+ * the three parts of a sampled unit are launches instead of graphs, each with the
+ * load and store of the state, and one unit's steps are taken before and after
+ * the timed units where these would not be in line with the coarse steps.
  * Synchronises `stream`. */
 mdlg_status lj_md_step_timed(lj_md* md, int64_t nunits, int32_t sample_every, double* ms_out, int32_t* n_out,
                              void* stream);

@@ -3892,6 +3892,11 @@ namespace {
 mdlg_status step_timed_resident(lj_md* md, int64_t nunits, int32_t sample_every, double* ms_out, int32_t* n_out,
                                 hipStream_t st) {
     if (md->vel_full) MDLG_HIP(run_resident(md, st, 1));
+    const int lead_in = steps_to_alignment(md);
+    if (lead_in > 0) {
+        MDLG_HIP(run_resident(md, st, lead_in));
+        --nunits;
+    }
     struct Unit {
         hipEvent_t ev[4];
         int lead, events;
@@ -3920,6 +3925,7 @@ mdlg_status step_timed_resident(lj_md* md, int64_t nunits, int32_t sample_every,
         if (e == hipSuccess) e = hipEventRecord(w.ev[3], st);
         units.back().events = (int)(md->events - ev0);
     }
+    if (e == hipSuccess && lead_in > 0) e = run_resident(md, st, md->K - lead_in);
     const hipError_t es = hipStreamSynchronize(st);
     if (e == hipSuccess) e = es;
     double sum[3] = {0.0, 0.0, 0.0};

@@ -723,6 +723,23 @@ def test_one_step_staged_tiles_equal_block_per_replica(sizes, phi, kT, kw):
         assert np.array_equal(x, y)
 
 
+def test_block_per_replica_times_the_same_parts_whatever_came_before():
+    """The timed parts of an interval (ordinary steps before its first event, the rest) do not depend on the steps
+    taken before the call."""
+    pos0, vel0, L = mi.initial_state(900, 0.0784, 20.0, 4)
+    for before in (0, 1, 13, 24, 25, 60):
+        sysm = gpu_system(pos0, vel0, L)
+        acc = sysm.attach_cg(20, 25)
+        K = sysm.info()["rebuild_every"]
+        assert K % 25 == 0
+        sysm.step(before)
+        ms, cnt = sysm.step_timed(9, 3)
+        assert (ms > 0).all() and list(cnt) == [2 * 24, 2 * K // 25, 2]
+        assert sysm.info()["steps_done"] == max(before, 1) + 9 * K and acc.events == sysm.info()["steps_done"] // 25
+        sysm.check()
+        sysm.close()
+
+
 def test_block_per_replica_reports_drift_and_times_steps():
     pos0, vel0, L = mi.initial_state(900, 0.0784, 20.0, 4)
     sysm = gpu_system(pos0, vel0, L)
