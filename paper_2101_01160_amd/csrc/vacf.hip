@@ -215,14 +215,15 @@ extern "C" mdlg_status mdlg_vacf(int32_t n_rep, const int64_t* offsets, int32_t 
     const bool staged = !few && lds + red_of(pt) <= kVacfLds;
     // particles of a block: whole groups, as many as leave about kVacfBlocks blocks
     const long long span = staged ? std::max<long long>(1, n_tot / pt / kVacfBlocks) * pt : kVacfBS;
-    if (span > (1 << 30)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
     std::vector<int> rep_block0(n_rep + 1, 0);
-    long long n_block = 0;
+    long long n_block = 0, groups = 0;
     for (int r = 0; r < n_rep; ++r) {
         const long long n = offsets[r + 1] - offsets[r];
         if (n < 0) return fail(MDLG_EINVAL, std::string(who) + "offsets must be non-decreasing");
         n_block += (n + span - 1) / span;
-        if (n_block >= (1 << 24)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
+        groups += (n + kVacfBS - 1) / kVacfBS;
+        // the limit of k_vacf's grid, whichever kernel takes the call
+        if (std::max(n_block, groups) >= (1 << 24)) return fail(MDLG_EINVAL, std::string(who) + "too many particles (grid limit)");
         rep_block0[r + 1] = (int)n_block;
     }
     if (n_block == 0) return MDLG_OK;

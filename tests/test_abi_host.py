@@ -180,3 +180,18 @@ def test_state_load_rejects_missing_and_foreign_files(tmp_path):
         assert _abi.lib().lj_md_load(ctypes.byref(h), str(path).encode(), None) == -1  # MDLG_EINVAL
         assert not h.value
         assert b"lj_md_load" in _abi.lib().mdlg_last_error()
+
+
+@pytest.mark.parametrize("n_snap,n_lag", [(100, 20), (20, 3), (20000, 3)])
+@pytest.mark.parametrize("sizes", [[2**32], [2**31, 2**31 - 300, 300], [1] + [2**32 - 256]])
+def test_vacf_refuses_the_same_sizes_on_every_route(n_snap, n_lag, sizes):
+    """2^24 blocks of 256 particles or more are refused before anything touches the device, also where the trajectories
+    would be staged in LDS."""
+    import ctypes as C
+
+    from paper_2101_01160_amd import _abi
+    off = (C.c_int64 * (len(sizes) + 1))(0, *np.cumsum(sizes).tolist())
+    lags = (C.c_int32 * n_lag)(*range(n_lag))
+    host = (C.c_double * 4)()
+    rc = _abi.lib().mdlg_vacf(len(sizes), off, n_snap, C.cast(host, C.c_void_p), n_lag, lags, C.cast(host, C.c_void_p), None)
+    assert rc == -1 and b"too many particles" in _abi.lib().mdlg_last_error()
