@@ -201,7 +201,7 @@ using namespace mdlg;
 // GPU the library runs on holds its own copy until the process ends.  In host
 // code this name stands for the device array but is not its address: kernels
 // get the address that hipGetSymbolAddress returned for the current device.
-constexpr long long kNoAllocMaxN = 1LL << 25;  // the entry point's limit
+constexpr long long kNoAllocMaxN = 1LL << 25;  // the entry point's limit (the scratch would do for any number)
 constexpr int kCgBS = 256;
 static __device__ __align__(256) unsigned char scratch[kCgScratch];
 
@@ -319,7 +319,7 @@ extern "C" mdlg_status mdlg_coarse_grain_noalloc(const mdlg_lattice* lat, double
     if (s != MDLG_OK) return s;
     if (n > kNoAllocMaxN)
         return fail(MDLG_EINVAL, "mdlg_coarse_grain_noalloc: n = " + std::to_string(n) + " exceeds the limit of " +
-                                     std::to_string(kNoAllocMaxN) + " particles of its fixed scratch");
+                                     std::to_string(kNoAllocMaxN) + " particles of one call");
     void* part = nullptr;
     s = scratch_of_current_device(&part);
     if (s != MDLG_OK) return s;

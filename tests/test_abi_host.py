@@ -195,3 +195,17 @@ def test_vacf_refuses_the_same_sizes_on_every_route(n_snap, n_lag, sizes):
     host = (C.c_double * 4)()
     rc = _abi.lib().mdlg_vacf(len(sizes), off, n_snap, C.cast(host, C.c_void_p), n_lag, lags, C.cast(host, C.c_void_p), None)
     assert rc == -1 and b"too many particles" in _abi.lib().mdlg_last_error()
+
+
+def test_noalloc_states_its_limit_as_the_calls_own():
+    """The limit is the interface's: the scratch of a call does not grow with the number of particles."""
+    import ctypes as C
+
+    from paper_2101_01160_amd import _abi
+    lat = _abi.Lattice(lx=8, reserved=0, u=(C.c_double * 2)(0.0, 0.0))
+    host = (C.c_double * 4)()
+    p = C.cast(host, C.c_void_p)
+    rc = _abi.lib().mdlg_coarse_grain_noalloc(C.byref(lat), 10.0, _abi.NOALLOC_MAX_N + 1, p, None, 0, p, None, 1, p, None,
+                                              None, None, None)
+    msg = _abi.lib().mdlg_last_error().decode()
+    assert rc == -1 and str(_abi.NOALLOC_MAX_N) in msg and "scratch" not in msg
