@@ -3833,7 +3833,12 @@ extern "C" mdlg_status lj_md_cg_detach(lj_md* md) {
     md->counts = nullptr;
     md->moments = nullptr;
     md->cell_acc = nullptr;
+    // at the end of an interval the next rebuild is due, whatever the interval
+    // now is: the last launch may have binned the particles for it (counts that
+    // only a rebuild takes and clears), or left no lists for further steps
+    const bool due = md->since_rebuild >= md->K;
     if (md->K_auto) md->K = md->K_base;
+    if (due) md->since_rebuild = md->K;
     return MDLG_OK;
 }
 

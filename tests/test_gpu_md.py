@@ -723,6 +723,32 @@ def test_one_step_staged_tiles_equal_block_per_replica(sizes, phi, kT, kw):
         assert np.array_equal(x, y)
 
 
+@pytest.mark.parametrize("n", [900, 4096])
+def test_detach_at_the_end_of_an_interval(n):
+    """Detaching the coarse-graining may lengthen the interval between rebuilds.  At an interval's end a rebuild stays
+    due: the particles are binned for it already (fused tiles), and there are no lists for further steps (block per
+    replica)."""
+    pos0, vel0, L = mi.initial_state(n, 0.0784, 20.0, 8)
+    sysm = gpu_system(pos0, vel0, L)
+    K0 = sysm.info()["rebuild_every"]
+    s_cg = (K0 - 1) // 2
+    sysm.attach_cg(20, s_cg)
+    K = sysm.info()["rebuild_every"]
+    assert K < K0 and K == 2 * s_cg
+    sysm.step(2 * K if n <= 2048 else 2 + 2 * K)  # a fused system takes a first step and one to its alignment
+    sysm.detach_cg()
+    sysm.step(3)
+    sysm.step(K0)
+    sysm.check()
+    steps = sysm.info()["steps_done"]
+    pos, vel, img = (_np(t) for t in sysm.state())
+    po, vo, io, _ = omd.md_run(pos0, vel0, np.zeros((n, 2), np.int64), L, steps)
+    up, uo = pos + L * img, po + L * io
+    # rounding grows by a factor of about ten in 100 steps of the 100-step comparisons' 1e-10
+    assert np.max(np.abs(up - uo)) <= 1e-8 * np.abs(uo).max() and np.max(np.abs(vel - vo)) <= 1e-8 * np.abs(vo).max()
+    sysm.close()
+
+
 def test_block_per_replica_times_the_same_parts_whatever_came_before():
     """The timed parts of an interval (ordinary steps before its first event, the rest) do not depend on the steps
     taken before the call."""
