@@ -1999,7 +1999,7 @@ struct ResArgs {
     int first;                  // the first step's velocity is a full-step one
     int s_cg;                   // 0: no coarse-graining
     int to_event;               // steps until the next event (1 .. s_cg)
-    long long event;            // index of that coarse step
+    int* done;                  // blocks that have finished (0 between launches)
 };
 
 // Exclusive scan over a block of whole waves; lds holds 32 ints.
@@ -2031,6 +2031,7 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
     __shared__ int hist[MDLG_NCOUNTS];
     __shared__ double red[kResBS / 64][4];
     __shared__ double macc[MDLG_NMOMENTS];
+    __shared__ long long event0;
     const int r = blockIdx.x, tid = threadIdx.x, BS = blockDim.x, lane = tid & 63, wave = tid >> 6;
     const RepDev& R = a.s.reps[r];
     // held in registers: a read through R after a barrier is a new load
@@ -2077,6 +2078,7 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
     };
     if (tid < MDLG_NCOUNTS) hist[tid] = 0;
     if (a.s_cg && tid < MDLG_NMOMENTS) macc[tid] = a.moments[r * MDLG_NMOMENTS + tid];
+    if (a.s_cg && tid == 0) event0 = *a.s.event_kw;
     int since = a.since;
     bool rebuilt = false;
 
@@ -2287,7 +2289,7 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
     __syncthreads();
 
     int to_event = a.to_event;
-    long long event = a.event;
+    long long event = a.s_cg ? event0 : 0;
     for (int st = 0; st < max(a.nsteps, 1); ++st) {
         if (since >= a.K) rebuild();
         if (a.nsteps == 0) break;
@@ -2400,6 +2402,13 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
     if (a.s_cg) {
         if (tid < MDLG_NCOUNTS && hist[tid]) a.counts[r * MDLG_NCOUNTS + tid] += (unsigned long long)hist[tid];
         if (tid < MDLG_NMOMENTS) a.moments[r * MDLG_NMOMENTS + tid] = macc[tid];
+        // the next coarse step's index, on the device: a launch that a caller has
+        // captured goes on from there.  Every block has read it before the last
+        // one to finish advances it.
+        if (tid == 0 && event != event0 && atomicAdd(a.done, 1) == (int)gridDim.x - 1) {
+            *a.done = 0;
+            *a.s.event_kw = event;
+        }
     }
 }
 
@@ -2905,6 +2914,7 @@ struct lj_md {
     int* cell_acc = nullptr;
     double* d_mpart = nullptr;
     long long* d_event_k = nullptr;
+    int* d_done = nullptr;  // see ResArgs
     hipStream_t cap = nullptr;
     std::map<GraphKey, GraphVal> graphs;
     // graphs of lj_md_step_timed: rebuild | ordinary steps | rest of a unit
@@ -3330,7 +3340,8 @@ hipError_t run_resident(lj_md* md, hipStream_t st, long long count) {
         a.first = md->vel_full ? 1 : 0;
         a.s_cg = md->cg_on ? md->s_cg : 0;
         a.to_event = md->cg_on ? (int)(md->s_cg - md->cg_t % md->s_cg) : 0;
-        a.event = md->events + 1;
+        a.s.event_kw = md->d_event_k;
+        a.done = md->d_done;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(md->R), dim3(md->res_bs), md->res_lds, st, a);
             return hipGetLastError();
@@ -3679,7 +3690,7 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
          A(dalloc(&md->cellof, md->S)) && A(dalloc(&md->cnt, md->C)) && A(dalloc(&md->cs, (size_t)md->C + 1)) &&
          A(dalloc(&md->bsum, md->nscan)) && A(dalloc(&md->d_err, 1)) && A(dalloc(&md->d_epart, (size_t)md->ntile * 4)) &&
          A(dalloc(&md->d_eout, (size_t)n_rep * 4)) && A(dalloc(&md->d_vmax, 1)) &&
-         A(dalloc(&md->d_mpart, part_tiles * MDLG_NMOMENTS)) && A(dalloc(&md->d_event_k, 1)) &&
+         A(dalloc(&md->d_mpart, part_tiles * MDLG_NMOMENTS)) && A(dalloc(&md->d_event_k, 1)) && A(dalloc(&md->d_done, 1)) &&
          A(hipStreamCreateWithFlags(&md->cap, hipStreamNonBlocking));
     if (ok && md->variant == 3) {
         static_assert(248 % kListU == 0 && 248 % kPassOne == 0 && kListPre <= 16, "list rows are read in whole passes");
@@ -3726,6 +3737,7 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
     if (e == hipSuccess && md->two_step)
         e = hipMemcpy(md->d_ptrep, ptrep.data(), sizeof(int) * md->npt, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemsetAsync(md->d_err, 0, sizeof(int), st);
+    if (e == hipSuccess) e = hipMemsetAsync(md->d_done, 0, sizeof(int), st);
     if (e == hipSuccess) e = hipMemsetAsync(md->cnt, 0, sizeof(int) * md->C, st);
     if (e == hipSuccess) e = hipMemsetAsync(md->d_vmax, 0, sizeof(unsigned long long), st);
     // reject non-finite inputs before they reach the cell index arithmetic
@@ -4292,7 +4304,7 @@ extern "C" void lj_md_destroy(lj_md* md) {
     void* ptrs[] = {md->d_reps, md->d_tile_rep, md->d_ttile_rep, md->d_tinfo, md->nbl, md->nbc, md->ncol, md->trange, md->lane_slot, md->pref, md->d_hpart, md->pos[0], md->pos[1], md->vel[0], md->vel[1], md->img[0],
                     md->img[1], md->id[0], md->id[1], md->snap[0], md->snap[1], md->key, md->rank, md->perm, md->permid,
                     md->cellof, md->cnt, md->cs, md->bsum, md->d_err, md->d_epart, md->d_eout, md->d_vmax,
-                    md->d_mpart, md->d_event_k, md->d_ptrep, md->plist, md->pcnt, md->tlist, md->tcnt};
+                    md->d_mpart, md->d_event_k, md->d_done, md->d_ptrep, md->plist, md->pcnt, md->tlist, md->tcnt};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete md;

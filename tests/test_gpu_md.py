@@ -749,6 +749,45 @@ def test_detach_at_the_end_of_an_interval(n):
     sysm.close()
 
 
+def test_block_per_replica_captured_by_the_caller():
+    """Steps with coarse-graining on a moving lattice, captured into a graph of the caller's and replayed with other
+    work in between: the coarse step's index goes on, as if the call had been made each time."""
+    import torch
+
+    import paper_2101_01160_amd as m
+    states = [mi.initial_state(n, 0.0784, 20.0, n) for n in (900, 300)]
+    pos, vel = (np.concatenate([s[k] for s in states]) for k in (0, 1))
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        def make():
+            b = m.LJSystem(_cuda(pos), _cuda(vel), params=[m.lj_params(s[0].shape[0], s[2]) for s in states])
+            return b, b.attach_cg([20, 11], 10, u=(0.37, -0.21))
+        a, acc_a = make()
+        b, acc_b = make()
+        n = 2 * a.info()["rebuild_every"]
+        a.step(n)
+        b.step(n)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        graph.capture_begin()
+        m.lj_md_step(a.handle, n, stream.cuda_stream)
+        graph.capture_end()
+        for _ in range(4):
+            graph.replay()
+            b.step(n)
+            torch.cuda.synchronize()
+            assert np.array_equal(_np(acc_a.counts), _np(acc_b.counts))
+            assert np.array_equal(_np(acc_a.moments), _np(acc_b.moments))
+            for x, y in zip(a.state(), b.state()):
+                assert np.array_equal(_np(x), _np(y))
+            assert np.array_equal(a.energy(), b.energy())
+        a.check()
+        b.check()
+        assert _np(acc_b.counts)[0, 0] < _np(acc_b.counts)[0].sum()
+        a.close()
+        b.close()
+
+
 def test_block_per_replica_times_the_same_parts_whatever_came_before():
     """The timed parts of an interval (ordinary steps before its first event, the rest) do not depend on the steps
     taken before the call."""
