@@ -105,8 +105,9 @@ typedef struct {
                                wherever the geometry allows; 3 = three wherever
                                it allows, else two.  0 also lets one block take
                                a whole replica through a call where every replica
-                               has at most 2048 particles.  Results are the same
-                               bit for bit.                                    */
+                               has at most 2048 particles, that is faster and the
+                               call is not a short one.  Results are the same bit
+                               for bit, moments to their rounding.             */
 } lj_params;
 
 typedef struct lj_md lj_md; /* opaque handle; owns all device state */
@@ -160,7 +161,9 @@ mdlg_status lj_md_cg_detach(lj_md* md);
  * the start of the next step, which is the same sequence of operations.
  * Repeated chunks are replayed from captured HIP graphs; replicas that one block
  * each takes through the call (fuse_steps 0) need none: a launch covers up to
- * 4096 steps. */
+ * 4096 steps.  For those, calls of a few steps take the step kernels instead;
+ * every step that ends a coarse step goes with a call of one block each, so that
+ * counts and moments do not depend on how a run is split into calls. */
 mdlg_status lj_md_step(lj_md* md, int64_t nsteps, void* stream);
 
 /* Advance the replicas by nunits x rebuild_every MD steps like lj_md_step,
@@ -213,7 +216,8 @@ typedef struct {
     int32_t block_size;
     double cell_width;      /* of replica 0                                     */
     int32_t steps_per_launch; /* ordinary MD steps per step-kernel launch on the replicas' geometry: 1, 2 or 3
-                                 (replicas of up to 2048 particles take whole calls in one launch by default) */
+                                 (small replicas take whole calls in one launch by default, see
+                                 fuse_steps: this is no measure of theirs) */
     int32_t reserved;
 } lj_md_info_t;
 mdlg_status lj_md_info(const lj_md* md, lj_md_info_t* info);

@@ -819,7 +819,8 @@ __global__ void k_tile_ranges(const int* __restrict__ cs, const RepDev* __restri
 // CELL (for the tile list builder) an entry is instead the neighbour's cell
 // relative to the particle's, (oy + 1) 3 + (ox + 1) in bits 12-15, and its
 // index within that cell in bits 0-11, and ncol[s] holds the particle's cell
-// column.  Also records the positions of the build for the next drift check.
+// column.  Also records the positions of the build for the next drift check
+// (pref; NULL where `pos` are the positions recorded then).
 // With STAGE (blocks of one tile, for the one-step kernel) the lists are words of
 // kPassOne entries (word j of the S columns at j S), an entry is the byte offset
 // of the neighbour's staged position, or its relative slot in a tile that does
@@ -859,7 +860,7 @@ __global__ __launch_bounds__(512) void k_nlist_build(const double2* __restrict__
     }
     const TileRanges* __restrict__ T = reinterpret_cast<const TileRanges*>(trange) + blockIdx.x;  // STAGE: one tile per block
     const bool staged = STAGE && trange && T->base[5] <= kStageMul * (int)blockDim.x;
-    if (act) pref[s] = p;
+    if (act && pref) pref[s] = p;
     const double invL = 1.0 / R.L;
     const double rl2 = R.w * R.w;
     if (CELL) ncol[s] = (unsigned short)cx;
@@ -1982,6 +1983,11 @@ constexpr int kResMax = 2 * kResBS;       // particles of one replica at most
 constexpr int kResLds = 156 * 1024;       // dynamic LDS at most
 constexpr int kResSteps = 4096;           // steps of one launch at most (a few milliseconds)
 constexpr int kResGroups = 16;            // list-length groups of the thread order
+// where it is faster than the tiles: see lj_md_init_batch
+constexpr double kResWork1 = 17000.0;     // particles x list length of a replica of up to kResBS particles
+constexpr double kResWork2 = 12000.0;     // and of a larger one
+constexpr long long kResManyN = 128000;   // particles of all replicas
+constexpr int kResCall = 20;              // calls of this many steps are its own in any case
 
 struct ResArgs {
     StepArgs s;
@@ -2000,6 +2006,8 @@ struct ResArgs {
     int s_cg;                   // 0: no coarse-graining
     int to_event;               // steps until the next event (1 .. s_cg)
     int* done;                  // blocks that have finished (0 between launches)
+    int* cellof;                // cell of each slot, or NULL
+    int deal;                   // whether to deal the lists left by the launch before to the threads by length
 };
 
 // Exclusive scan over a block of whole waves; lds holds 32 ints.
@@ -2072,10 +2080,8 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
         else if (2 * e < -n) e += n;
         a.nbl[(long long)j * S + slot0 + q] = (short)e;
     };
-    auto get = [&](int j, int q) __attribute__((always_inline)) {
-        const int e = q + a.nbl[(long long)j * S + slot0 + q];
-        return e < 0 ? e + n : (e >= n ? e - n : e);
-    };
+    auto slot_of = [&](int e) __attribute__((always_inline)) { return e < 0 ? e + n : (e >= n ? e - n : e); };
+    auto get = [&](int j, int q) __attribute__((always_inline)) { return slot_of(q + a.nbl[(long long)j * S + slot0 + q]); };
     if (tid < MDLG_NCOUNTS) hist[tid] = 0;
     if (a.s_cg && tid < MDLG_NMOMENTS) macc[tid] = a.moments[r * MDLG_NMOMENTS + tid];
     if (a.s_cg && tid == 0) event0 = *a.s.event_kw;
@@ -2259,30 +2265,48 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
         rebuilt = true;
     };
 
-    // lists left by the launch before
+    // lists left by the launch before: rows are loaded eight at a time, the first
+    // without waiting for the lists' lengths (maxnb >= 16)
     if (since < a.K) {
+        constexpr int U8 = 8;
+        short row[NP][U8];
 #pragma unroll
         for (int k = 0; k < NP; ++k) {
-            const int q = tid + k * BS;
-            if (q >= n) continue;
-            nn[k] = a.nbc[slot0 + q];  // (pref is that of slot q)
-            for (int j = 0; j < min(nn[k], a.rows); ++j) lst[j * a.cap + q] = (unsigned short)get(j, q);
+            const int q = tid + k * BS, s = slot0 + (q < n ? q : 0);
+#pragma unroll
+            for (int u = 0; u < U8; ++u) row[k][u] = a.nbl[(long long)u * S + s];
+            nn[k] = q < n ? a.nbc[s] : 0;  // (pref is that of slot q)
+        }
+#pragma unroll
+        for (int k = 0; k < NP; ++k) {
+            const int q = tid + k * BS, rows = min(nn[k], a.rows);
+            for (int j0 = 0; j0 < rows; j0 += U8) {
+                if (j0 > 0) {
+#pragma unroll
+                    for (int u = 0; u < U8; ++u) row[k][u] = a.nbl[(long long)min(j0 + u, a.maxnb - 1) * S + slot0 + q];
+                }
+#pragma unroll
+                for (int u = 0; u < U8; ++u)
+                    if (j0 + u < rows) lst[(j0 + u) * a.cap + q] = (unsigned short)slot_of(q + row[k][u]);
+            }
         }
         __syncthreads();
-        deal();
-        // every particle's state is still in global memory: read it again in the new order
+        if (a.deal) {
+            deal();
+            // every particle's state is still in global memory: read it again in the new order
 #pragma unroll
-        for (int k = 0; k < NP; ++k) {
-            const int q = tid + k * BS < n ? order[tid + k * BS] : n;
-            slot[k] = q;
-            const int s = slot0 + (q < n ? q : 0);
-            p[k] = a.s.pin[s];
-            v[k] = a.s.vel[s];
-            img[k] = a.img[s];
-            id[k] = a.id[s];
-            if (a.s_cg) snap[k] = a.s.snap[s];
-            pref[k] = a.pref[s];
-            nn[k] = q < n ? a.nbc[s] : 0;
+            for (int k = 0; k < NP; ++k) {
+                const int q = tid + k * BS < n ? order[tid + k * BS] : n;
+                slot[k] = q;
+                const int s = slot0 + (q < n ? q : 0);
+                p[k] = a.s.pin[s];
+                v[k] = a.s.vel[s];
+                img[k] = a.img[s];
+                id[k] = a.id[s];
+                if (a.s_cg) snap[k] = a.s.snap[s];
+                pref[k] = a.pref[s];
+                nn[k] = q < n ? a.nbc[s] : 0;
+            }
         }
         lists();
     }
@@ -2392,6 +2416,7 @@ __global__ __launch_bounds__(kResBS) void k_resident(ResArgs a) {
             a.id[s] = id[k];
             a.pref[s] = pref[k];
             a.nbc[s] = (unsigned char)nn[k];
+            if (a.cellof) a.cellof[s] = R.cell0 + cell_coord(pref[k].y, inv_w, nc) * nc + cell_coord(pref[k].x, inv_w, nc);
             if (since < a.K) {
                 for (int j = 0; j < min(nn[k], a.rows); ++j) put(j, slot[k], lst[j * a.cap + slot[k]]);
             }
@@ -2873,9 +2898,15 @@ struct lj_md {
     unsigned char* tcnt = nullptr;    // [npt][kPairCap]
     double2* pref = nullptr;  // positions at the list build
     int maxnb = 0;
-    // a block per replica for whole calls (see k_resident); steps_per_launch is
-    // then what the replicas' geometry would allow the tiles
+    // a block per replica for calls of res_min steps or more (see k_resident), with
+    // lists of its own; shorter calls take the tiles (see tile_call)
     bool resident = false;
+    int res_min = 0;
+    short* nbl_slot = nullptr;          // [maxnb][S]
+    unsigned char* nbc_slot = nullptr;  // [S], behind nbl_slot
+    bool tile_lists = false;            // whether the tiles' lists, and those, are of the last rebuild
+    bool slot_lists = false;
+    int quick_calls = 0;                // calls below res_min in a row
     int spl = 1;
     int res_bs = 0, res_np = 0, res_cap = 0, res_cells = 0, res_rows = 0;
     size_t res_lds = 0;
@@ -2914,7 +2945,7 @@ struct lj_md {
     int* cell_acc = nullptr;
     double* d_mpart = nullptr;
     long long* d_event_k = nullptr;
-    int* d_done = nullptr;  // see ResArgs
+    int* d_done = nullptr;  // see ResArgs; behind d_err
     hipStream_t cap = nullptr;
     std::map<GraphKey, GraphVal> graphs;
     // graphs of lj_md_step_timed: rebuild | ordinary steps | rest of a unit
@@ -3148,7 +3179,44 @@ hipError_t launch_observe(lj_md* md, hipStream_t st, double2* opos, double2* ove
     return hipGetLastError();
 }
 
-hipError_t launch_rebuild(lj_md* md, hipStream_t st) {
+// The neighbour lists of the step kernels for `pos`, the positions of a rebuild
+// (recorded in `pref` unless it is NULL).  The tile lists take entries by cell
+// and index within the cell, the one-step kernel words of staged offsets (or of
+// slot offsets, where trange is not laid out).
+void launch_lists(lj_md* md, hipStream_t st, const double2* pos, double2* pref) {
+    const int S = md->S;
+    auto lists = [&](auto kernel, int grid, int bs) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(bs), 0, st, pos, (const int*)md->cs, (const RepDev*)md->d_reps,
+                           (const int*)md->d_tile_rep, md->BS, S, md->maxnb, md->nbl, md->nbc, md->ncol, pref,
+                           (const int*)md->trange, md->lane_slot, md->d_err);
+    };
+    if (md->variant == 3 && md->two_step) {
+        lists(k_nlist_build<LIST_CELL>, (S + 255) / 256, 256);
+    } else if (md->variant == 3) {
+        if (md->trange) hipLaunchKernelGGL(k_tile_ranges, dim3((md->ntile + 63) / 64), dim3(64), 0, st, (const int*)md->cs,
+                           (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, (const int*)md->cellof, md->BS, md->ntile,
+                           md->trange);
+        lists(k_nlist_build<LIST_STAGE>, md->ntile, md->BS);
+    }
+    if (md->two_step)
+        hipLaunchKernelGGL(k_pair_build<kPairBuildBS>, dim3(md->npt), dim3(kPairBuildBS), 0, st, (const int*)md->cs,
+                           (const RepDev*)md->d_reps, (const int*)md->d_ptrep, (const short*)md->nbl,
+                           (const unsigned char*)md->nbc, (const unsigned short*)md->ncol, S, md->maxnb, md->rings,
+                           md->plist, md->pcnt, md->tlist, md->tcnt, md->d_err);
+    md->tile_lists = true;
+}
+
+// The same lists for the block-per-replica kernel: slot offsets.
+void launch_slot_lists(lj_md* md, hipStream_t st, const double2* pos, double2* pref) {
+    hipLaunchKernelGGL(k_nlist_build<LIST_SLOT>, dim3((md->S + 255) / 256), dim3(256), 0, st, pos, (const int*)md->cs,
+                       (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, md->BS, md->S, md->maxnb, md->nbl_slot,
+                       md->nbc_slot, (unsigned short*)nullptr, pref, (const int*)nullptr, (unsigned short*)nullptr, md->d_err);
+    md->slot_lists = true;
+}
+
+// With `slots` (resident handles), lists for the block-per-replica kernel in
+// place of the others.
+hipError_t launch_rebuild(lj_md* md, hipStream_t st, bool slots = false) {
     const int S = md->S, C = md->C;
     const int o = md->opar;
     const int grid = md->ntile;
@@ -3187,29 +3255,9 @@ hipError_t launch_rebuild(lj_md* md, hipStream_t st) {
     hipLaunchKernelGGL(k_place, dim3((S + 255) / 256), dim3(256), 0, st, (const int*)md->cs, (const int*)md->key,
                        (const int*)md->perm, (const int*)md->permid, S, b,
                        md->variant != 3 || md->trange ? md->cellof : nullptr);
-    // the tile lists take entries by cell and index within the cell, the
-    // one-step kernel words of staged offsets (or of slot offsets, where
-    // trange is not laid out), the block-per-replica kernel slot offsets
-    auto lists = [&](auto kernel, int grid, int bs) {
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(bs), 0, st, (const double2*)b.pos_n, (const int*)md->cs,
-                           (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, md->BS, S, md->maxnb, md->nbl, md->nbc,
-                           md->ncol, md->pref, (const int*)md->trange, md->lane_slot, md->d_err);
-    };
-    if (md->variant == 3 && md->two_step) {
-        lists(k_nlist_build<LIST_CELL>, (S + 255) / 256, 256);
-    } else if (md->variant == 3 && md->resident) {
-        lists(k_nlist_build<LIST_SLOT>, (S + 255) / 256, 256);
-    } else if (md->variant == 3) {
-        if (md->trange) hipLaunchKernelGGL(k_tile_ranges, dim3((md->ntile + 63) / 64), dim3(64), 0, st, (const int*)md->cs,
-                           (const RepDev*)md->d_reps, (const int*)md->d_tile_rep, (const int*)md->cellof, md->BS, md->ntile,
-                           md->trange);
-        lists(k_nlist_build<LIST_STAGE>, md->ntile, md->BS);
-    }
-    if (md->two_step)
-        hipLaunchKernelGGL(k_pair_build<kPairBuildBS>, dim3(md->npt), dim3(kPairBuildBS), 0, st, (const int*)md->cs,
-                           (const RepDev*)md->d_reps, (const int*)md->d_ptrep, (const short*)md->nbl,
-                           (const unsigned char*)md->nbc, (const unsigned short*)md->ncol, S, md->maxnb, md->rings,
-                           md->plist, md->pcnt, md->tlist, md->tcnt, md->d_err);
+    md->slot_lists = md->tile_lists = false;
+    if (slots) launch_slot_lists(md, st, b.pos_n, md->pref);
+    else launch_lists(md, st, b.pos_n, md->pref);
     md->ppar ^= 1;
     md->opar ^= 1;
     md->vpar ^= 1;
@@ -3310,14 +3358,37 @@ int steps_to_alignment(const lj_md* md) {
     int period = 1;
     if (md->s_cg <= md->K) period = md->K % md->s_cg == 0 ? md->s_cg : 1;
     else period = md->s_cg % md->K == 0 ? md->K : 1;
-    const long long residue = (md->two_step && period >= 3) ? 2 : 0;
+    const long long residue = (md->two_step && !md->resident && period >= 3) ? 2 : 0;
     const long long r = ((md->cg_t - residue) % period + period) % period;
     return r == 0 ? 0 : (int)(period - r);
+}
+
+// Whether the tiles take a call of n steps of a resident handle.  What a launch
+// of k_resident adds to its steps (state and lists in and out) makes it slower
+// than they are below res_min steps.  Steps with an event are always its own, so
+// that the moments' sums do not depend on how a run is split into calls.  Where
+// it has rebuilt the cells, lists of the tiles cost two launches: only from the
+// second short call in a row.
+bool tile_call(lj_md* md, long long n) {
+    const bool quick = n < md->res_min && n < md->K && !(md->cg_on && md->cg_t % md->s_cg + n >= md->s_cg);
+    md->quick_calls = quick ? std::min(md->quick_calls + 1, 2) : 0;
+    return quick && (md->tile_lists || md->quick_calls > 1);
+}
+
+hipError_t run_tiles(lj_md* md, hipStream_t st, long long count) {
+    if (!md->tile_lists && md->since_rebuild < md->K) launch_lists(md, st, md->pref, nullptr);
+    return run_steps(md, st, count);
 }
 
 // `count` steps of a resident handle (count 0: a due rebuild alone).
 hipError_t run_resident(lj_md* md, hipStream_t st, long long count) {
     hipError_t e = hipSuccess;
+    // counts that the last launch of the tiles binned are a rebuild's to take and clear
+    if (md->binned) e = launch_rebuild(md, st, true);
+    if (e != hipSuccess) return e;
+    if (!md->slot_lists && md->since_rebuild < md->K) launch_slot_lists(md, st, md->pref, nullptr);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
     do {
         ResArgs a{};
         a.s = make_args(md);
@@ -3325,9 +3396,10 @@ hipError_t run_resident(lj_md* md, hipStream_t st, long long count) {
         a.img = md->img[md->opar];
         a.id = md->id[md->opar];
         a.cs = md->cs;
-        a.nbl = md->nbl;
-        a.nbc = md->nbc;
+        a.nbl = md->nbl_slot;
+        a.nbc = md->nbc_slot;
         a.pref = md->pref;
+        a.cellof = md->trange ? md->cellof : nullptr;
         a.counts = md->counts;
         a.moments = md->moments;
         a.cap = md->res_cap;
@@ -3340,6 +3412,10 @@ hipError_t run_resident(lj_md* md, hipStream_t st, long long count) {
         a.first = md->vel_full ? 1 : 0;
         a.s_cg = md->cg_on ? md->s_cg : 0;
         a.to_event = md->cg_on ? (int)(md->s_cg - md->cg_t % md->s_cg) : 0;
+        // a few steps gain less by it than the 3 us that it takes (three steps of 256
+        // and 1024 particles 8.2 and 12.7 us without, 9.6 and 14.2 with it; six 11 and
+        // 20, 13 and 19); events sum the moments in its order
+        a.deal = md->res_np > 1 || a.nsteps > 8 - md->res_bs / 256 || (md->cg_on && a.to_event <= a.nsteps) ? 1 : 0;
         a.s.event_kw = md->d_event_k;
         a.done = md->d_done;
         auto launch = [&](auto kernel) {
@@ -3352,6 +3428,10 @@ hipError_t run_resident(lj_md* md, hipStream_t st, long long count) {
         else e = md->f32 ? launch(k_resident<true, 1, 4>) : launch(k_resident<false, 1, 4>);
         if (e != hipSuccess) return e;
         // the kernel's own schedule: a rebuild before the step that finds the lists K steps old
+        if (md->since_rebuild >= md->K || md->since_rebuild + a.nsteps > md->K) {
+            md->tile_lists = false;
+            md->slot_lists = true;
+        }
         if (a.nsteps == 0) {
             if (md->since_rebuild >= md->K) md->since_rebuild = 0;
             break;
@@ -3447,6 +3527,28 @@ long long eager_len(const lj_md* md, long long nsteps) {
     if (align > 0) return std::min<long long>(align, nsteps);
     if (md->use_graphs && nsteps >= md->K) return 0;
     return nsteps;
+}
+
+// The steps from which a call is as fast with one block per replica as on the
+// other step kernels (at most kResCall).  A launch of k_resident costs `fixed`
+// beside its steps, mostly the first pass through its code and the lists, so the
+// line is fixed / (their time per step - its own), from these fits in us to
+// calls of 1 to 100 steps, 64 to 2048 particles at phi = 0.08, 0.2 and 0.4 and 1
+// to 512 replicas.  (Measured at phi = 0.2: 512 particles 4.5 per step in calls
+// of three, 4.9 one step per launch; 1024 5.6 and 4.9, in calls of six 4.1 and
+// 4.8; 256 of them 6.6 and 7.7 in calls of three.)  Where the geometry allows
+// fused tiles that clustering could overflow, calls of 2 to about 10 steps are
+// slower than on those: 1024 particles at phi = 0.08 9.8 in calls of two against
+// 7.0, 19 in calls of six against 17, 2048 9.3 and 30 against 7.1 and 17.
+int shortest_resident_call(double work, double list, bool two, int n_rep, double n_total, double slots, bool fused) {
+    const double w = work / 1000.0, rounds = std::ceil(n_rep / 256.0);
+    const double step = rounds * (two ? 1.2 + w / 4.3 : 1.0 + w / 3.6);
+    const double fixed = two ? 10.5 + 0.4 * w : 3.0 + 0.35 * w;
+    const double tiles = fused ? std::max(2.7, 2.1 + n_total / 80000.0) :
+                                 std::max(5.1, 3.3 + slots / 53000.0) + (list > 10.0 ? 0.9 : 0.0);
+    if (tiles <= step) return kResCall;
+    const double line = fused ? 2.0 + 4.0 / (tiles - step) : std::max(two ? 3.0 : 2.0, 1.0 + fixed / (tiles - step));
+    return (int)std::min((double)kResCall, line);
 }
 
 mdlg_status check_params(const lj_params& p, int r) {
@@ -3640,16 +3742,27 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
         md->maxnb = std::min(248, ((int)std::ceil(2.0 * mean_max + 16.0) + 7) / 8 * 8);
     }
     if (md->variant == 3 && p[0].fuse_steps == 0) {
-        // A block per replica where every replica fits one: a single replica of
-        // 2048 particles takes 2.5 us per step that way and 2.5 us on tiles over
-        // several compute units (1500 dense ones 7.0 and 7.1 us), smaller ones
-        // and batches less (256 x 2048: 2.9 against 9.0 us).
+        // A block per replica where every replica fits one and that is faster.  Its
+        // step is the work of one compute unit, particles x list length, which the
+        // tiles spread over several: replicas of 1024, 1500 and 2048 particles took
+        // 1.6, 2.3 and 2.6 us per step at phi = 0.08 (2.9, 2.9 and 2.8 on tiles), 2.5,
+        // 3.4 and 4.8 at 0.2 (4.5, 4.8, 4.5) and 5.6, 6.8 (1500) at 0.4 (6.3, 6.0), as
+        // products of 3, 4.5, 6; 8, 11, 16; 17 and 23 thousand.  With two particles
+        // to a thread (above 1024) the line is lower: 1100 at 0.4, 17 thousand, take
+        // 6.1 (5.5 to 5.9).  From 128,000 particles in all the tiles fill the chip
+        // (128 x 1500 at 0.4: 6.9 against 9.0).
         int nmax = 0, cmax = 0;
         for (int r = 0; r < n_rep; ++r) {
             nmax = std::max(nmax, md->reps[r].d.n);
             cmax = std::max(cmax, std::min(md->reps[r].d.nc, 1000) * std::min(md->reps[r].d.nc, 1000));
         }
-        if (nmax <= kResMax) {
+        double work = 0.0;
+        for (int r = 0; r < n_rep; ++r) {
+            const RepDev& d = md->reps[r].d;
+            work = std::max(work, 3.14159265358979 * d.w * d.w * (double)d.n / (d.L * d.L) * d.n);
+        }
+        const bool faster = work <= (nmax <= kResBS ? kResWork1 : kResWork2) || poff >= kResManyN;
+        if (nmax <= kResMax && faster) {
             md->res_bs = std::min(kResBS, (nmax + 63) / 64 * 64);
             md->res_np = (nmax + md->res_bs - 1) / md->res_bs;
             md->res_cap = (nmax + 63) / 64 * 64;
@@ -3663,9 +3776,13 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
             md->resident = md->res_rows >= std::max(8.0, std::min((double)md->maxnb, mean_max + 4.0 * std::sqrt(mean_max)));
         }
         if (md->resident) {
-            // one step kernel for all its steps, lists of slot offsets
-            md->two_step = md->three_step = false;
-            md->npt = 0;
+            // Shorter calls take the step kernels: one step per launch, or fused tiles
+            // where the particles of a replica fit one however they cluster.
+            if (nmax > kPairCap) {
+                md->two_step = md->three_step = false;
+                md->npt = 0;
+            }
+            md->res_min = shortest_resident_call(work, mean_max, nmax > kResBS, n_rep, (double)poff, md->S, md->two_step);
             auto allow = [&](const void* k) { return hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, kResLds); };
             const void* kernels[] = {(const void*)k_resident<true, 2, 2>, (const void*)k_resident<false, 2, 2>,
                                      (const void*)k_resident<true, 1, 2>, (const void*)k_resident<false, 1, 2>,
@@ -3688,9 +3805,9 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
              A(dalloc(&md->id[b], md->S)) && A(dalloc(&md->snap[b], md->S));
     ok = ok && A(dalloc(&md->key, md->S)) && A(dalloc(&md->rank, md->S)) && A(dalloc(&md->perm, md->S)) && A(dalloc(&md->permid, md->S)) &&
          A(dalloc(&md->cellof, md->S)) && A(dalloc(&md->cnt, md->C)) && A(dalloc(&md->cs, (size_t)md->C + 1)) &&
-         A(dalloc(&md->bsum, md->nscan)) && A(dalloc(&md->d_err, 1)) && A(dalloc(&md->d_epart, (size_t)md->ntile * 4)) &&
+         A(dalloc(&md->bsum, md->nscan)) && A(dalloc(&md->d_err, 2)) && A(dalloc(&md->d_epart, (size_t)md->ntile * 4)) &&
          A(dalloc(&md->d_eout, (size_t)n_rep * 4)) && A(dalloc(&md->d_vmax, 1)) &&
-         A(dalloc(&md->d_mpart, part_tiles * MDLG_NMOMENTS)) && A(dalloc(&md->d_event_k, 1)) && A(dalloc(&md->d_done, 1)) &&
+         A(dalloc(&md->d_mpart, part_tiles * MDLG_NMOMENTS)) && A(dalloc(&md->d_event_k, 1)) &&
          A(hipStreamCreateWithFlags(&md->cap, hipStreamNonBlocking));
     if (ok && md->variant == 3) {
         static_assert(248 % kListU == 0 && 248 % kPassOne == 0 && kListPre <= 16, "list rows are read in whole passes");
@@ -3707,7 +3824,10 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
             return destroy_on_fail(md, fail(MDLG_EINVAL, "lj_md_init: neighbour lists of this size exceed 2^30 "
                                                          "entries; use step_kernel 1"));
         ok = A(dalloc(&md->nbl, (size_t)md->maxnb * md->S)) && A(dalloc(&md->nbc, md->S)) && A(dalloc(&md->pref, md->S));
-        if (ok && !md->two_step && !md->resident && mean_max >= kStageMean)
+        if (ok && md->resident)
+            ok = A(dalloc(&md->nbl_slot, (size_t)md->maxnb * md->S + md->S / 2));  // S is even: whole blocks
+        md->nbc_slot = (unsigned char*)(md->nbl_slot + (size_t)md->maxnb * md->S);
+        if (ok && !md->two_step && mean_max >= kStageMean)
             ok = A(dalloc(&md->trange, (size_t)md->ntile * kRangeInts)) && A(dalloc(&md->lane_slot, md->S));
         if (ok && md->two_step)
             ok = A(dalloc(&md->d_ptrep, md->npt)) && A(dalloc(&md->plist, (size_t)md->npt * kPairCap)) &&
@@ -3736,8 +3856,8 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
     if (e == hipSuccess) e = hipMemcpy(md->d_ttile_rep, ttrep.data(), sizeof(int) * md->TT, hipMemcpyHostToDevice);
     if (e == hipSuccess && md->two_step)
         e = hipMemcpy(md->d_ptrep, ptrep.data(), sizeof(int) * md->npt, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemsetAsync(md->d_err, 0, sizeof(int), st);
-    if (e == hipSuccess) e = hipMemsetAsync(md->d_done, 0, sizeof(int), st);
+    md->d_done = md->d_err + 1;
+    if (e == hipSuccess) e = hipMemsetAsync(md->d_err, 0, 2 * sizeof(int), st);
     if (e == hipSuccess) e = hipMemsetAsync(md->cnt, 0, sizeof(int) * md->C, st);
     if (e == hipSuccess) e = hipMemsetAsync(md->d_vmax, 0, sizeof(unsigned long long), st);
     // reject non-finite inputs before they reach the cell index arithmetic
@@ -3790,7 +3910,7 @@ extern "C" mdlg_status lj_md_init_batch(lj_md** out, int32_t n_rep, const lj_par
     }
     md->K_base = md->K;
     // first rebuild (no drift check)
-    if (launch_rebuild(md, st) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
+    if (launch_rebuild(md, st, md->resident) != hipSuccess || hipStreamSynchronize(st) != hipSuccess)
         return destroy_on_fail(md, fail(MDLG_EHIP, "lj_md_init: initial cell sort failed"));
     md->vel_full = true;
     *out = md;
@@ -3860,7 +3980,7 @@ extern "C" mdlg_status lj_md_step(lj_md* md, int64_t nsteps, void* stream) {
     if (nsteps < 0) return fail(MDLG_EINVAL, "lj_md_step: nsteps must be >= 0");
     hipStream_t st = (hipStream_t)stream;
     if (md->resident) {
-        if (nsteps > 0) MDLG_HIP(run_resident(md, st, nsteps));
+        if (nsteps > 0) MDLG_HIP(tile_call(md, nsteps) ? run_tiles(md, st, nsteps) : run_resident(md, st, nsteps));
         return MDLG_OK;
     }
     while (nsteps > 0) {
@@ -4301,10 +4421,10 @@ extern "C" void lj_md_destroy(lj_md* md) {
     if (!md) return;
     clear_graphs(md);
     if (md->cap) (void)hipStreamDestroy(md->cap);
-    void* ptrs[] = {md->d_reps, md->d_tile_rep, md->d_ttile_rep, md->d_tinfo, md->nbl, md->nbc, md->ncol, md->trange, md->lane_slot, md->pref, md->d_hpart, md->pos[0], md->pos[1], md->vel[0], md->vel[1], md->img[0],
+    void* ptrs[] = {md->d_reps, md->d_tile_rep, md->d_ttile_rep, md->d_tinfo, md->nbl, md->nbc, md->nbl_slot, md->ncol, md->trange, md->lane_slot, md->pref, md->d_hpart, md->pos[0], md->pos[1], md->vel[0], md->vel[1], md->img[0],
                     md->img[1], md->id[0], md->id[1], md->snap[0], md->snap[1], md->key, md->rank, md->perm, md->permid,
                     md->cellof, md->cnt, md->cs, md->bsum, md->d_err, md->d_epart, md->d_eout, md->d_vmax,
-                    md->d_mpart, md->d_event_k, md->d_done, md->d_ptrep, md->plist, md->pcnt, md->tlist, md->tcnt};
+                    md->d_mpart, md->d_event_k, md->d_ptrep, md->plist, md->pcnt, md->tlist, md->tcnt};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
     delete md;

@@ -749,6 +749,49 @@ def test_detach_at_the_end_of_an_interval(n):
     sysm.close()
 
 
+@pytest.mark.parametrize("sizes,phi,kT,s_cg,kw", [
+    ([512], 0.0784, 20.0, 0, {"rebuild_every": 20}), ([512, 300], 0.0784, 20.0, 7, {"rebuild_every": 20}),
+    ([1000], 0.35, 5.0, 0, {"rebuild_every": 25}), ([1000, 640], 0.35, 5.0, 9, {"rebuild_every": 25, "block_size": 64}),
+    ([700], 0.2, 5.0, 50, {"rebuild_every": 16, "force_bits": 32}), ([1500], 0.0784, 20.0, 0, {"rebuild_every": 60}),
+    ([1500, 1100], 0.0784, 20.0, 30, {"rebuild_every": 60}), ([1024], 0.0784, 20.0, 11, {"rebuild_every": 3}),
+    ([1025] * 126, 0.4, 5.0, 0, {"rebuild_every": 60}), ([64], 0.1, 5.0, 0, {"rebuild_every": 30}),
+])
+def test_short_and_long_calls_of_small_replicas(sizes, phi, kT, s_cg, kw):
+    """Long calls by one block per replica and short ones by tiles, in turn: single short calls between long ones and
+    several in a row, rebuilds due in either, at their ends and between them, and tiles that have binned the particles
+    for a rebuild that the other kernel finds due; events in short calls.  Against one step per launch, rebuilt at the
+    same steps, the same states and counts bit for bit; moments bit for bit between two splits."""
+    import paper_2101_01160_amd as m
+    print(f"short and long calls {sizes[:2]} x {len(sizes)} phi={phi} s_cg={s_cg} {kw}", flush=True)
+    K = kw["rebuild_every"]
+    base = {n: mi.initial_state(n, phi, kT, 30 + n) for n in set(sizes)}
+    pos, vel = (np.concatenate([base[n][k] for n in sizes]) for k in (0, 1))
+    mixed = [1, 1, 2, K, 1, K - 1, 2 * K + 3, 1, 1, 1, 2, 3, 1, 90, 2, 2, 61, 5, 4, 1]
+    mixed += [1] * (-sum(mixed) % K)                  # single steps up to the end of an interval
+    mixed += [70, 1, 1, 3 * K - 72 % K, 1, 1, 1, 1, K + 1, 2, 47, 1, 46, 1, 1]
+    total = sum(mixed)
+    out = []
+    for fuse, calls in ((1, [1] * total), (0, mixed), (0, [total]), (0, [1] * total)):
+        if len(sizes) > 100 and fuse == 0 and calls is not mixed:
+            continue
+        b = m.LJSystem(_cuda(pos), _cuda(vel), params=[m.lj_params(n, base[n][2], fuse_steps=fuse, **kw) for n in sizes])
+        acc = b.attach_cg([max(7, int(base[n][2] / 2.0)) for n in sizes], s_cg, u=(0.1, -0.3)) if s_cg else None
+        for c in calls:
+            b.step(c)
+        b.check()
+        assert b.info()["steps_done"] == total
+        out.append([_np(t) for t in b.state()] + [_np(b.forces())] + ([_np(acc.counts), _np(acc.moments)] if s_cg else []))
+        b.close()
+    for other in out[1:]:
+        for k, (x, y) in enumerate(zip(out[0], other)):
+            if k == 5:
+                for r in range(len(sizes)):
+                    assert_moments_close(y[r], x[r])
+                assert np.array_equal(y, out[1][5])
+            else:
+                assert np.array_equal(x, y)
+
+
 def test_block_per_replica_captured_by_the_caller():
     """Steps with coarse-graining on a moving lattice, captured into a graph of the caller's and replayed with other
     work in between: the coarse step's index goes on, as if the call had been made each time."""
