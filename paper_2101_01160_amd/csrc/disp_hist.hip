@@ -11,13 +11,13 @@
 //
 // The work is HBM-bound: 48 bytes of snapshot data per particle pair and two
 // LDS counter increments.  A block owns one replica, one lag and a share of its
-// work items (512 particles of one snapshot pair); its per-axis histograms sit
-// in LDS (32-bit, in a few copies so that the lanes of a wave seldom meet in a
-// bin) and are added to the int64 output with one global atomic per non-empty
-// bin.  About 512 blocks in all keep those few: with a block per 256 particles
-// and chunk of pairs the 890,000 global atomics of 4 x 99,856 particles, 8 pairs
-// and 96 bins took most of 33 us; 17.7 us here (20.6 us with 1024 blocks of half
-// the threads).  The tables of up to 512 replicas travel as kernel arguments: no
+// work items (up to 512 particles of one snapshot pair, see hist_shares.h); its
+// per-axis histograms sit in LDS (32-bit, in a few copies so that the lanes of a
+// wave seldom meet in a bin) and are added to the int64 output with one global
+// atomic per non-empty bin.  About 512 blocks in all keep those few: with a block
+// per 256 particles and chunk of pairs the 890,000 global atomics of 4 x 99,856
+// particles, 8 pairs and 96 bins took most of 33 us; 18.7 us here (20.6 us with
+// 1024 blocks of half the threads).  The tables of up to 512 replicas travel as kernel arguments: no
 // allocation and no copy, which with the wait for them took half of its 81 us (40
 // us now).
 #include <algorithm>

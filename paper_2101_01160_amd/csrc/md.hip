@@ -1963,15 +1963,16 @@ __global__ __launch_bounds__(BS) void k_pair_build(const int* __restrict__ cs, c
 //
 // A replica of up to kResMax particles fits in one compute unit: positions in
 // LDS (ping-pong), everything else of a particle in the registers of one
-// thread, neighbour lists in LDS.  The block then takes all steps of a call
+// thread, neighbour lists in LDS (rows beyond its room in global memory).  The block then takes all steps of a call
 // (up to kResSteps) with one barrier per step, rebuilding its cells and lists
 // every K steps by itself: no launches, no halo and no HBM traffic in between.
 // With three steps per launch on tiles a launch of such a system took 6.1 us
 // (512 particles) to 11.5 us (256 replicas of 998), the seven launches of a
-// rebuild 33 us; the time per step including rebuilds was 2.9 us (512
-// particles) and 5.7 us (256 x 998), here 1.1 and 1.75 us.  A step without any
-// pair takes 0.35 us (barrier, position write and read, update); the rest is
-// the issue of FP64 instructions, about 25 per list entry.
+// rebuild 33 us, and calls of 400 and 391 steps 1150 and 2210 us: 2.9 and 5.6 us
+// per step, rebuilds and the state's readout included; here 500 and 750 us, 1.25
+// and 1.9.  A step without any pair takes 0.35 us (barrier, position write and
+// read, update); the rest is the issue of FP64 instructions, about 25 per list
+// entry.  Which handles and calls take it: lj_md_init_batch and tile_call.
 //
 // Slots, cells and lists are those of the other step kernels (particles within
 // a cell ordered by caller index, list entries in cell order), and so is the
@@ -3537,9 +3538,10 @@ long long eager_len(const lj_md* md, long long nsteps) {
 // to 512 replicas.  (Measured at phi = 0.2: 512 particles 4.5 per step in calls
 // of three, 4.9 one step per launch; 1024 5.6 and 4.9, in calls of six 4.1 and
 // 4.8; 256 of them 6.6 and 7.7 in calls of three.)  Where the geometry allows
-// fused tiles that clustering could overflow, calls of 2 to about 10 steps are
-// slower than on those: 1024 particles at phi = 0.08 9.8 in calls of two against
-// 7.0, 19 in calls of six against 17, 2048 9.3 and 30 against 7.1 and 17.
+// fused tiles that clustering could overflow, calls of 2 to about 10 steps (25 for
+// the largest) are slower than on those: 1024 particles at phi = 0.08 9.8 in calls
+// of two against 7.0, 19 in calls of six against 17, 2048 10.5 and 30 against 7.1
+// and 17.
 int shortest_resident_call(double work, double list, bool two, int n_rep, double n_total, double slots, bool fused) {
     const double w = work / 1000.0, rounds = std::ceil(n_rep / 256.0);
     const double step = rounds * (two ? 1.2 + w / 4.3 : 1.0 + w / 3.6);

@@ -61,7 +61,7 @@ __device__ __forceinline__ float wave_sum_f(float v) {
 // (k fastest), so that a wave's load is one contiguous run.  Forward products
 // have k = a layer's inputs, backward ones k = its outputs; K and N are padded
 // to whole fragments with zeros.  Read as 64-byte pieces of 16 rows instead,
-// the training kernel below took 27 us for 2048 samples (16.6 so) and inference
+// the training kernel below took 27 us for 2048 samples (16.7 so) and inference
 // 59 us for 65,536 (41 so).
 constexpr long kFrag = 512;
 constexpr long kF1 = 0, kF2 = kF1 + 16 * kFrag, kF3 = kF2 + 128 * kFrag, kF4 = kF3 + 128 * kFrag,
@@ -123,8 +123,8 @@ struct TrainBufs {
 // and the weights come from L2 straight into operand registers, a whole layer's
 // share of a wave (16 vectors of 16 bytes per lane) in flight during the
 // products and the epilogue of the layer before.  The bound is what a compute
-// unit reads from L2, 0.6 MB of weights per block, and the chain of layers: 16.6
-// us for 2048 samples (13.5 us for 32).
+// unit reads from L2, 0.6 MB of weights per block, and the chain of layers: 16.7
+// us for 2048 samples (13.5 us for 32; 17.5 us in a long training run).
 //
 // Wave w owns columns 32 w .. 32 w + 31 (two 16 x 16 tiles) of a hidden layer.
 // MFMA 16x16x32 lane layout: lane l holds A(row l%16, k 8*(l/16) .. +7),
@@ -310,8 +310,9 @@ __global__ __launch_bounds__(kTrainBS) __attribute__((amdgpu_waves_per_eu(2))) v
 // chunk of the samples, into the partials part[split][parameter]; the blocks of
 // a layer's first row of tiles also take the column sums, as the products of a
 // row of ones.  Launch latency and operand latency bound it at these sizes:
-// 8.4 us for 2048 samples in 8 splits (11.8 us with 64-byte pieces of rows for
-// operands); the sums and the update after it 4.8 us.
+// 8.2 us for 2048 samples in 8 splits (11.8 us with 64-byte pieces of rows for
+// operands); the sums and the update after it 4.9 us (7.6 and 4.8 us in a long
+// training run).
 constexpr int kTK = 32;            // k step, and the padding of the samples
 constexpr int kWgTiles = 4 + 16 + 16 + 4;
 

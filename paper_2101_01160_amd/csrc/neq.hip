@@ -17,7 +17,8 @@
 //                  lattices beyond LDS; displacements outside D2Q49 are counted
 //                  per wave by a ballot and added with one atomic per wave;
 //   k_neq_xi       Xi sums as f[k+1](x + v_i) - f[k](x) over the periodic
-//                  lattice, one thread per output element (HBM-bound stencil).
+//                  lattice, a block per step, velocity and 1024 cells (HBM-bound
+//                  stencil).
 #include <algorithm>
 #include <cmath>
 
